@@ -18,7 +18,16 @@ using namespace bla;
 
 constexpr size_t kAlign = 256;
 constexpr size_t kMaxSummaryBytes = size_t(256) << 20;  // cap on per-block summary scratch
-constexpr int kMaxPairSegments = 16;                     // segments per sequence on the pair kernel
+// How the pair kernel gets the states entering the segments (Plan::enter).  Measured on whole
+// calls at d = M = 64 (us; combine / state pass / scan): 16 sequences of 500 tokens 31 / 22 / -,
+// of 2000 tokens 53 (one-unit kernels) / 35 / 45, of 4096 60 (one-unit) / 42 / 49, of 16384
+// 139 (one-unit) / 108 / 87, of 65536 488 (one-unit) / 390 / 270; 4 of 8192 tokens (127 slots)
+// 99 (one-unit) / 52 / 46; 32 of 4096 tokens 75 / 67 / -; 128 of 4096 tokens (4 segments) 134 / 135 / -; 256 of
+// 512 tokens 33 / 36 / -.  The state pass walks a sequence's chunks one after the other, so it is
+// for short sequences; the combination reads O(segments^2) summaries, so it is for few segments.
+constexpr int kMaxPassChunks = 80;      // most chunks of a sequence for the state pass
+constexpr int kMaxCombineSegments = 4;  // most segments combined where the state pass could run
+constexpr int kMaxPairSegments = 8;     // most segments combined at all; past it, the scan
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
@@ -147,14 +156,6 @@ void make_plan(const bla_params* p, bool step, Plan* pl)
     }
     if (!step && units > 0 && pl->nch > 1) {
         const int cus = device_cu_count();
-        // The pair kernel combines every preceding segment summary in each unit's prologue,
-        // which reads O(nseg^2) summaries per sequence.  Where filling the device would take
-        // more than kMaxPairSegments segments (few, long sequences), the one-unit kernels run
-        // instead: per-block summaries and a scan, linear in the number of segments.
-        if (pl->pair && units * kMaxPairSegments < (long long)cus * pl->upw) {
-            pl->pair = 0;
-            pl->upw = 1;
-        }
         const long long target = (long long)cus * pl->upw;  // units that fill every CU once
         if (units < target) {
             long long want = (target + units - 1) / units;
@@ -163,6 +164,11 @@ void make_plan(const bla_params* p, bool step, Plan* pl)
             nseg = (pl->nch + cps - 1) / cps;
             pl->nseg = nseg;
             pl->cps = cps;
+            pl->enter = kEnterScan;
+            if (pl->pair)
+                pl->enter = nseg > kMaxCombineSegments && pl->nch <= kMaxPassChunks ? kEnterPass
+                            : nseg > kMaxPairSegments                                              ? kEnterScan
+                                                                                                   : kEnterCombine;
             if (nseg > 1) {
                 // Blocks per segment: enough summary workgroups to fill the device, within
                 // the scratch cap; always a divisor of cps.
@@ -530,6 +536,7 @@ static bla_status forward_impl(const bla_params* p, const double* T, const void*
     a.cps = pl.cps;
     a.cpb = pl.cpb;
     a.nbs = pl.nbs;
+    a.entered = pl.enter != kEnterCombine;
     a.t0 = pl.t0;
     a.scale = pl.scale;
     a.in_b = si[0];
@@ -540,7 +547,7 @@ static bla_status forward_impl(const bla_params* p, const double* T, const void*
     a.out_t = (int)so[2];
     if (pl.nseg > 1 && launch_summary(pl, a, s) != hipSuccess) return BLA_ERR_HIP;
     if (!mark(2)) return BLA_ERR_HIP;
-    if (pl.nseg > 1 && !pl.pair && launch_scan(pl, a, s) != hipSuccess) return BLA_ERR_HIP;
+    if (pl.nseg > 1 && pl.enter == kEnterScan && launch_scan(pl, a, s) != hipSuccess) return BLA_ERR_HIP;
     if (!mark(3)) return BLA_ERR_HIP;
     if (launch_forward(pl, a, s) != hipSuccess) return BLA_ERR_HIP;
     if (!mark(4)) return BLA_ERR_HIP;

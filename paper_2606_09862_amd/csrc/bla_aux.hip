@@ -10,10 +10,13 @@
 
 namespace bla {
 
-// 2 pi (m j mod T) / T, exact up to the final rounding of the division.
-__device__ __forceinline__ double mode_phase(long long mj, double T)
+// cos and sin of 2 pi m j / T, rT = 1 / T.  The revolutions are reduced to [0, 1) in double
+// (an error of a few 2^-53 of m j / T, far below the float32 that the tables hold); fmod's
+// long division and the argument reduction of sincos took most of the kernel's time.
+__device__ __forceinline__ void mode_phase(long long mj, double rT, double* sn, double* cs)
 {
-    return 2.0 * M_PI * fmod((double)mj, T) / T;
+    const double x = (double)mj * rT;
+    sincospi(2.0 * (x - floor(x)), sn, cs);
 }
 
 // One thread per angle: a (head, j, m) phase with j = 0..C for the per-head tables,
@@ -34,7 +37,7 @@ __global__ __launch_bounds__(kThreads) void tables_kernel(TableArgs a)
         const int rem = (int)(gid % (J * MP));
         const int j = rem / MP, m = rem % MP, h = a.h0 + hl;
         double sn = 0.0, cs = 0.0;
-        if (m < a.M) sincos(mode_phase((long long)m * j, a.T[hl]), &sn, &cs);
+        if (m < a.M) mode_phase((long long)m * j, 1.0 / a.T[hl], &sn, &cs);
         float* E32 = a.E32 + (size_t)h * (C + 1) * MP2;
         E32[(size_t)j * MP2 + m] = (float)cs;
         E32[(size_t)j * MP2 + MP + m] = (float)sn;
@@ -71,7 +74,7 @@ __global__ __launch_bounds__(kThreads) void tables_kernel(TableArgs a)
         } else {
             const int m = k - a.SP;
             double sn = 0.0, cs = 0.0;
-            if (m < a.M) sincos(mode_phase((long long)m * a.Lblk, Tp), &sn, &cs);
+            if (m < a.M) mode_phase((long long)m * a.Lblk, 1.0 / Tp, &sn, &cs);
             a.rotblk[(size_t)h * MP2 + m] = (float)cs;
             a.rotblk[(size_t)h * MP2 + MP + m] = (float)sn;
         }
@@ -85,9 +88,8 @@ __global__ __launch_bounds__(kThreads) void tables_kernel(TableArgs a)
         float ca = 0.f, sa = 0.f;
         if (s < a.S && m < a.M) {
             const double cm = (m == 0 ? 1.0 : 2.0) / (2.0 * a.M - 1.0);
-            const double ph = 2.0 * M_PI * (double)(((long long)m * s) % a.S) / (double)a.S;
             double sn, cs;
-            sincos(ph, &sn, &cs);
+            sincospi(2.0 * (double)((m * s) % a.S) / (double)a.S, &sn, &cs);
             ca = (float)(cm * cs);
             sa = (float)(a.negB ? -cm * sn : cm * sn);
         }
@@ -103,7 +105,7 @@ __global__ __launch_bounds__(kThreads) void tables_kernel(TableArgs a)
         // cos | sin of 2 pi k / S: the slot matrices are c_m times these at k = m s mod S
         const int k = (int)(gid - n_head - n_misc - n_ab);
         double sn = 0.0, cs = 0.0;
-        if (k < a.S) sincos(2.0 * M_PI * (double)k / (double)a.S, &sn, &cs);
+        if (k < a.S) sincospi(2.0 * (double)k / (double)a.S, &sn, &cs);
         a.trig[k] = (float)cs;
         a.trig[a.SP + k] = (float)sn;
     }
@@ -243,8 +245,69 @@ __global__ __launch_bounds__(kThreads) void scan_kernel(FwdArgs a, int MP, int D
     }
 }
 
+// The scan over the lane-ordered segment summaries of the pair path (bla_forward_pair.h), in
+// place: summary g becomes the pre-rotated state entering segment g + 1.  One thread per four
+// consecutive complex elements (a 16-byte piece of the real and of the imaginary part): four
+// head-dim elements of one mode (keys) or four modes of one head-dim element (values).  Bound by
+// the latency of its loads, which are issued eight summaries at a time.
+__global__ __launch_bounds__(kThreads) void scan_pair_kernel(FwdArgs a, int MP, int D)
+{
+    const int per = 2 * MP * D / 4;  // pieces per (b, h): keys, then values
+    const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (gid >= (long long)a.B * a.H * per) return;
+    const int bh = (int)(gid / per), h = bh % a.H;
+    const int isv = (int)(gid % per) / (per / 2), e = (int)(gid % per) % (per / 2);
+    const int lane = e % 64, g = lane / 16, r = lane % 16, tile = e / 64, dt = tile % (D / 16), mt = tile / (D / 16);
+    const size_t U = (size_t)4 * MP * D, re = (size_t)isv * 2 * MP * D + 4 * (size_t)e, im = re + (size_t)MP * D;
+    const float* E1 = a.E32 + ((size_t)h * (a.C + 1) + 1) * 2 * MP;
+    const float* rb = a.rotblk + (size_t)h * 2 * MP;
+    const float* sin_ = isv ? a.sv_in : a.sk_in;
+    floatx4 cb, sb, zr = zero4(), zi = zero4();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int m = isv ? 16 * mt + 4 * g + q : 16 * mt + r;
+        const int d = isv ? 16 * dt + r : 16 * dt + 4 * g + q;
+        cb[q] = rb[m];
+        sb[q] = rb[MP + m];
+        if (sin_ && m < a.M) {
+            const float xr = sin_[(((size_t)bh * 2 + 0) * a.M + m) * D + d];
+            const float xi = sin_[(((size_t)bh * 2 + 1) * a.M + m) * D + d];
+            const float c1 = E1[m], s1 = E1[MP + m];
+            zr[q] = c1 * xr - s1 * xi;
+            zi[q] = s1 * xr + c1 * xi;
+        }
+    }
+    float* S = a.summ + (size_t)bh * a.nbs * U;
+    constexpr int AHEAD = 8;
+    for (int j0 = 0; j0 < a.nbs; j0 += AHEAD) {
+        floatx4 sr[AHEAD], si[AHEAD];
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const size_t j = (size_t)min(j0 + u, a.nbs - 1);
+            sr[u] = ld4f(S + j * U + re);
+            si[u] = ld4f(S + j * U + im);
+        }
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            if (j0 + u < a.nbs) {
+                const floatx4 nr = cb * zr - sb * zi + sr[u];
+                zi = sb * zr + cb * zi + si[u];
+                zr = nr;
+                st4f(S + (size_t)(j0 + u) * U + re, zr);
+                st4f(S + (size_t)(j0 + u) * U + im, zi);
+            }
+        }
+    }
+}
+
 hipError_t launch_scan(const Plan& p, const FwdArgs& a, hipStream_t s)
 {
+    if (p.pair) {
+        const long long np = (long long)p.B * p.H * 2 * p.MP * p.D / 4;
+        hipLaunchKernelGGL(scan_pair_kernel, dim3((unsigned)((np + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, a,
+                           p.MP, p.D);
+        return hipGetLastError();
+    }
     long long n = (long long)p.B * p.H * 2 * p.MP * p.D;
     dim3 grid((unsigned)((n + kThreads - 1) / kThreads));
     hipLaunchKernelGGL(scan_kernel, grid, dim3(kThreads), 0, s, a, p.MP, p.D, p.cps / p.cpb);

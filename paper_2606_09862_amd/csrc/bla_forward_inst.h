@@ -122,6 +122,14 @@ template <typename T, int D, int MP, int SP> constexpr int pair_units()
     template <> hipError_t Launch<T, D, MP, SP>::summary(const Plan& p, const FwdArgs& a, hipStream_t s) \
     {                                                                                                   \
         if constexpr (pair_units<T, D, MP, SP>() > 0) {                                                 \
+            if (p.pair && p.enter == kEnterPass) {                                                      \
+                const dim3 sgrid((unsigned)state_pass_grid<D, MP>((long long)p.B * p.H));               \
+                if (p.cps == 1)                                                                         \
+                    hipLaunchKernelGGL((state_pair_kernel<D, MP, true>), sgrid, dim3(StatePass<D, MP>::NTHR), 0, s, a);  \
+                else                                                                                    \
+                    hipLaunchKernelGGL((state_pair_kernel<D, MP, false>), sgrid, dim3(StatePass<D, MP>::NTHR), 0, s, a); \
+                return hipGetLastError();                                                               \
+            }                                                                                           \
             if (p.pair) {                                                                               \
                 hipLaunchKernelGGL((summary_pair_kernel<D, MP>),                                        \
                                    dim3((unsigned)summary_grid_x<D, MP>((long long)p.B * p.nbs), (unsigned)p.H),  \

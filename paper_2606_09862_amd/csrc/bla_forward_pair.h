@@ -27,7 +27,8 @@
 //    the one row [cos | sin](m w P) for every token of the chunk.
 //  * Sequences are split into segments.  summary_pair_kernel reduces every segment
 //    but the last to its summary (step (10) alone from a zero state); a unit then
-//    starts from the preceding summaries combined in its prologue,
+//    starts from the preceding summaries combined in its prologue (or, with many
+//    segments, from the states that a scan or state_pair_kernel left),
 //        Z'_g = rho^{L_s} o (... (rho^{L_s} o (rho Z_in) + S_0) ...) + S_{g-1},
 //    which is the state recurrence taken a whole segment (L_s tokens) at a time.
 #pragma once
@@ -532,6 +533,161 @@ __attribute__((amdgpu_waves_per_eu(SumPair<D, MP>::MINB * SumPair<D, MP>::NW / 4
     }
 }
 
+// ---------------------------------------------------------------------------------
+// Entering states: one pass over a sequence's chunks in order, leaving the pre-rotated state that
+// enters segment g >= 1 in summary slot g - 1 (sum_tile layout), from the call's input state.
+// Against the summaries and their combination (in the forward prologue or a scan) it reads K and V
+// once as well but writes each state once and reads none back.
+//
+// The state's accumulator tiles are independent, so the work splits into (b, h, K or V, 16
+// columns) workgroups with one wave per mode tile; each wave carries one complex tile.  Bound by
+// the chain of chunks: per chunk the product with the phase table starts from zero (it does not
+// wait for the state) and only the rotation is serial.  At 16 sequences of 32 chunks (d = M = 64)
+// it takes 15 us, 4 of them for its 32 MB of states, where summaries and scan took 13 + 13.  CPI chunks are staged per barrier, NPF
+// stages ahead in registers.
+template <int D, int MP> struct StatePass {
+    static constexpr int C = kChunk, KBC = C / 32, NMT = MP / 16, DS = D / 16, NTHR = 64 * NMT;
+    static constexpr int CPI = NTHR > 128 ? NTHR / 128 : 1;      // chunks per stage
+    static constexpr int PPT = 2 * C * CPI / NTHR;               // 16-byte pieces per thread and stage
+    static constexpr int NPF = 4;
+    static constexpr int STAGE = C * 16 * CPI;                   // elements
+    static_assert(NPF % 2 == 0, "the LDS buffer parity follows the unrolled stage index");
+};
+
+// EVERY: one chunk per segment.  Every chunk's state is then stored, unconditionally: a store
+// under a branch leaves the compiler without a bound on the memory operations in flight, and it
+// waits for the store before the next staged load.
+template <int D, int MP, bool EVERY>
+__global__ __launch_bounds__((StatePass<D, MP>::NTHR)) void state_pair_kernel(FwdArgs a)
+{
+    using P = StatePass<D, MP>;
+    using F = bf16x8;
+    constexpr int C = P::C, KBC = P::KBC, NPF = P::NPF, CPI = P::CPI, DS = P::DS;
+    // rows of 16 elements: the 8 rows of a transposed half-wave read fill the 64 banks
+    __shared__ __attribute__((aligned(16))) bf16 lds[2 * P::STAGE];
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, r = lane & 15;
+    const int mt = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // the DS column slices of a tensor take workgroup indices 8 apart: one XCD, one fetch per line
+    const int xq = blockIdx.x / 8, ds = xq % DS, job = (xq / DS) * 8 + blockIdx.x % 8;
+    if (job >= 2 * a.B * a.H) return;  // grid padding (whole workgroup, before any barrier)
+    const int isv = job & 1, bh = job >> 1, h = bh % a.H;
+    const int ts = a.in_t;
+    const bf16* src = (const bf16*)(isv ? a.v : a.k) + fwd_in_base(a, bh) + ds * 16;
+    const int nch = (a.nseg - 1) * a.cps;  // chunks walked, all full
+
+    F st[NPF][P::PPT];
+    auto load = [&](F (&x)[P::PPT], int n) {  // chunks n .. n + CPI - 1 (clamped to the last)
+#pragma unroll
+        for (int i = 0; i < P::PPT; ++i) {
+            const int u = tid + i * P::NTHR, row = u / 2;
+            const int tok = min(n, nch - 1) * C + row;
+            x[i] = *reinterpret_cast<const F*>(src + (size_t)min(tok, nch * C - 1) * ts + 8 * (u % 2));
+        }
+    };
+    auto store = [&](const F (&x)[P::PPT], int buf) {
+#pragma unroll
+        for (int i = 0; i < P::PPT; ++i)
+            *reinterpret_cast<F*>(lds + (size_t)buf * P::STAGE + 8 * (tid + i * P::NTHR)) = x[i];
+    };
+#pragma unroll
+    for (int i = 0; i < NPF; ++i) load(st[i], i * CPI);
+
+    // conj(rho^i) fragments of the wave's mode tile, held for the whole walk
+    F ef[KBC][2];
+    const bf16* E = (const bf16*)a.Etab + (size_t)h * C * 2 * MP + 16 * mt + r;
+#pragma unroll
+    for (int kb = 0; kb < KBC; ++kb)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const bf16* row = E + (size_t)(32 * kb + 16 * (e / 4) + 4 * g + e % 4) * 2 * MP;
+            ef[kb][0][e] = row[0];
+            ef[kb][1][e] = row[MP];
+        }
+    // rho^C of the lane's elements (K: four head dims of mode 16 mt + r; V: modes 16 mt + 4 g + e),
+    // and the state entering the sequence, pre-rotated
+    const float* E32h = a.E32 + (size_t)h * (C + 1) * 2 * MP;
+    const float* sin_ = isv ? a.sv_in : a.sk_in;
+    floatx4 cc, ss, re = zero4(), im = zero4();
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int m = isv ? 16 * mt + 4 * g + e : 16 * mt + r, d = isv ? 16 * ds + r : 16 * ds + 4 * g + e;
+        cc[e] = E32h[(size_t)C * 2 * MP + m];
+        ss[e] = E32h[(size_t)C * 2 * MP + MP + m];
+        if (sin_ && m < a.M) {
+            const float xr = sin_[(((size_t)bh * 2 + 0) * a.M + m) * D + d];
+            const float xi = sin_[(((size_t)bh * 2 + 1) * a.M + m) * D + d];
+            const float c1 = E32h[2 * MP + m], s1 = E32h[3 * MP + m];
+            re[e] = c1 * xr - s1 * xi;
+            im[e] = s1 * xr + c1 * xi;
+        }
+    }
+    float* S = a.summ + (size_t)bh * a.nbs * 4 * MP * D + sum_tile<D, MP>(2 * isv, mt, ds) + 4 * lane;
+    store(st[0], 0);
+    load(st[0], NPF * CPI);
+    __syncthreads();
+
+    int left = a.cps;  // chunks until the next segment starts
+    for (int n0 = 0; n0 < nch; n0 += NPF * CPI) {
+#pragma unroll
+        for (int s = 0; s < NPF; ++s) {
+            const int n = n0 + s * CPI;
+            {   // the next stage into the other buffer (last read before the previous barrier)
+                const int s1 = (s + 1) % NPF;
+                store(st[s1], s1 & 1);
+                load(st[s1], n + (1 + NPF) * CPI);
+            }
+            const bf16* X = lds + (size_t)(s & 1) * P::STAGE;
+            floatx4 yr[CPI], yi[CPI];
+#pragma unroll
+            for (int q = 0; q < CPI; ++q) {
+                yr[q] = yi[q] = zero4();
+#pragma unroll
+                for (int kb = 0; kb < KBC; ++kb) {
+                    const F x = ld_frag_tr(X + (size_t)q * C * 16, 16, 0, kb, g, r);
+                    if (isv) {
+                        yr[q] = mma(ef[kb][0], x, yr[q]);
+                        yi[q] = mma(ef[kb][1], x, yi[q]);
+                    } else {
+                        yr[q] = mma(x, ef[kb][0], yr[q]);
+                        yi[q] = mma(x, ef[kb][1], yi[q]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < CPI; ++q) {
+                const floatx4 zr = re + yr[q], zi = im + yi[q];
+                if constexpr (EVERY) {  // past the last chunk: that chunk's state again
+                    const bool ok = n + q < nch;
+                    const floatx4 nr = cc * zr - ss * zi, ni = ss * zr + cc * zi;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        re[e] = ok ? nr[e] : re[e];
+                        im[e] = ok ? ni[e] : im[e];
+                    }
+                    float* Sn = S + (size_t)min(n + q, nch - 1) * 4 * MP * D;
+                    st4f(Sn, re);
+                    st4f(Sn + (size_t)MP * D, im);
+                } else if (n + q < nch) {
+                    re = cc * zr - ss * zi;
+                    im = ss * zr + cc * zi;
+                    if (--left == 0) {
+                        left = a.cps;
+                        st4f(S, re);
+                        st4f(S + (size_t)MP * D, im);
+                        S += (size_t)4 * MP * D;
+                    }
+                }
+            }
+            __syncthreads();  // the next stage visible; this one's buffer free
+        }
+    }
+}
+
+template <int D, int MP> constexpr long long state_pass_grid(long long units)
+{
+    return (2 * units + 7) / 8 * 8 * StatePass<D, MP>::DS;
+}
+
 // grid: ceil(B*nseg/U) x H workgroups of 256*U threads; workgroup (x, h) runs the
 // units 2x and 2x+1 (U = 2) of head h.  Units are numbered over (b, i) with
 // i = 0, 1, 2, 3, ... taking segments 0, nseg-1, 1, nseg-2, ..., so that the two units
@@ -645,13 +801,14 @@ __global__ __launch_bounds__((256 * Pair<D, MP, SP>::U)) void forward_pair_kerne
     // ---- state entering the unit's segment (pre-rotated: Z' = rho Z)
     PState<D, MP, SP> Zk, Zv;
     const float* E1 = sRho;
+    const bool entered = a.entered && seg > 0;  // the state is in summary slot seg - 1
 #pragma unroll
     for (int o = 0; o < OWN; ++o) {
         const int mt = wl + P::WPU * o;
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
             Zk[o][0][dt] = Zk[o][1][dt] = Zv[o][0][dt] = Zv[o][1][dt] = zero4();
-            if (mt < NMT && active) {
+            if (mt < NMT && active && !entered) {
                 const int m = 16 * mt + r;
                 floatx4 kr = zero4(), ki = zero4(), vr = zero4(), vi = zero4();
                 if (a.sk_in && m < a.M) {
@@ -677,10 +834,26 @@ __global__ __launch_bounds__((256 * Pair<D, MP, SP>::U)) void forward_pair_kerne
             }
         }
     }
+    if (active && entered) {
+        const float* S = a.summ + ((size_t)bh * a.nbs + seg - 1) * 4 * MP * D;
+#pragma unroll
+        for (int o = 0; o < OWN; ++o) {
+            const int mt = wl + P::WPU * o;
+            if (mt < NMT) {
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) {
+                        Zk[o][p][dt] = ld4f(S + sum_tile<D, MP>(p, mt, dt) + 4 * (tid & 63));
+                        Zv[o][p][dt] = ld4f(S + sum_tile<D, MP>(2 + p, mt, dt) + 4 * (tid & 63));
+                    }
+            }
+        }
+    }
     // combine the summaries of the blocks before this segment (Horner, block by block);
     // the next block's summary is loaded while the current one is combined (every load
     // unconditional, indices clamped, so each wait covers exactly one block's loads)
-    if (active && seg > 0) {
+    if (active && seg > 0 && !a.entered) {
         const int nblk = seg * (a.cps / a.cpb);
         const float* rb = a.rotblk + (size_t)h * 2 * MP;
         const float* Sb = a.summ + (size_t)bh * a.nbs * 4 * MP * D;

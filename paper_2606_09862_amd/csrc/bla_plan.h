@@ -14,6 +14,11 @@ constexpr int kChunk = 64;      // default tokens per chunk of the parallel form
 constexpr int kThreads = 256;   // 4 waves of 64 lanes per workgroup
 constexpr int kMaxHeadsPerTableLaunch = 64;
 
+// The states entering the segments: combined from the summaries in the forward kernel's prologue
+// (pair kernel), left by a scan over the summaries, or left by one pass over the sequence's
+// chunks instead of the summaries (pair kernel).
+enum { kEnterCombine = 0, kEnterScan = 1, kEnterPass = 2 };
+
 // Sizes and workspace layout of one forward / step call.
 struct Plan {
     int B, H, L, D, M, S;
@@ -26,6 +31,7 @@ struct Plan {
     int nseg, cps;       // segments per sequence, chunks per segment
     int upw;             // sequence units per forward workgroup (1, or 2 for the pair kernel)
     int pair;            // 1 if the bf16 pair kernel runs the forward pass
+    int enter;           // where the states entering segments 1.. come from (kEnter*), for nseg > 1
     int anchor;          // 1: slots anchored at absolute phase 0 (Sec. 3.3), 0: at the current token
     int cpb, nbs;        // chunks per summarised block, summarised blocks per sequence
     size_t unit_floats;  // floats of one full (k and v) pre-rotated state: 4*MP*D
@@ -110,6 +116,7 @@ struct FwdArgs {
     int B, H, L, M;
     int C;        // tokens per chunk (the per-head phase table E32 has C + 1 rows)
     int nch, nseg, cps, cpb, nbs;
+    int entered;  // pair kernel: summary slot g - 1 holds the state entering segment g
     long long t0;
     float scale;  // score scale (applied by the pair kernel; folded into ABs otherwise)
     int anchor;   // 1: slots anchored at absolute phase 0 (Sec. 3.3)
