@@ -123,7 +123,8 @@ bla_status check_periods(const bla_params* p, const double* T)
     return BLA_OK;
 }
 
-void make_plan(const bla_params* p, bool step, Plan* pl)
+// one_per_cu: aim at one sequence unit per compute unit instead of upw.
+void make_plan_for(const bla_params* p, bool step, bool one_per_cu, Plan* pl)
 {
     memset(pl, 0, sizeof(*pl));
     pl->B = p->B;
@@ -156,7 +157,7 @@ void make_plan(const bla_params* p, bool step, Plan* pl)
     }
     if (!step && units > 0 && pl->nch > 1) {
         const int cus = device_cu_count();
-        const long long target = (long long)cus * pl->upw;  // units that fill every CU once
+        const long long target = (long long)cus * (one_per_cu ? 1 : pl->upw);  // units that fill every CU once
         if (units < target) {
             long long want = (target + units - 1) / units;
             int nseg = (int)(want < pl->nch ? want : pl->nch);
@@ -213,6 +214,20 @@ void make_plan(const bla_params* p, bool step, Plan* pl)
     pl->off_fErev = off;  off = align_up(off + fh);
     pl->off_fTw = off;    off = align_up(off + fh);
     pl->total = off;
+}
+
+void make_plan(const bla_params* p, bool step, Plan* pl)
+{
+    make_plan_for(p, step, false, pl);
+    // 128 padded slots at 64 modes and d = 64 run two units per workgroup, and take the segment
+    // summaries that go with them, only because the slot matrix is held folded.  Half the
+    // segments (the one unit per workgroup that an unfolded matrix leaves room for) need half
+    // the scratch: where that is what fits bla_forward_noalloc's fixed array, the plan keeps to it.
+    if (pl->pair && pl->upw == 2 && pl->SP == 128 && pl->total > BLA_NOALLOC_SCRATCH_BYTES) {
+        Plan alt;
+        make_plan_for(p, step, true, &alt);
+        if (alt.total <= BLA_NOALLOC_SCRATCH_BYTES) *pl = alt;
+    }
 }
 
 // step: a decode step needs the phase rows j = 0, 1 only.  reuse: skip the launch when the
@@ -530,6 +545,7 @@ static bla_status forward_impl(const bla_params* p, const double* T, const void*
     a.H = pl.H;
     a.L = pl.L;
     a.M = pl.M;
+    a.S = pl.S;
     a.C = pl.C;
     a.nch = pl.nch;
     a.nseg = pl.nseg;

@@ -341,6 +341,67 @@ __device__ __forceinline__ void twiddle_h(halfx4 c, halfx4 n, floatx4& re, float
     im = i;
 }
 
+// Slot folding.  Slots s and S - s share a row of the slot matrices: A[S-s] = A[s] and
+// B[S-s] = -B[s] (cos and sin of 2 pi m s / S).  With p = A uc and q = B us the two scores are
+// p + q and p - q, and with e_s the slot weights the readout is
+//     a = sum_s (e_s + e_{S-s}) A[s],   b = sum_s (e_s - e_{S-s}) B[s]   over s <= S/2,
+// so the products with the slot matrices, and the table that they read, are half as large.
+// Measured (us, before and after): 128 sequences of 4096 tokens at d = M = 64 with 127 slots
+// 194 -> 131 (the smaller table leaves room for two units per compute unit), with 64 slots
+// 126 -> 124; 64 of 2048 at d = 128, M = 64, 127 slots 284 -> 103 (the tiles now fit the pair
+// kernel); 16 of 65536 at d = M = 128 slots 1094 -> 1057; 32 of 1000 in float32, M = 32, 63
+// slots 79 -> 72.  Where the padded slot count SP is 32, its one 32-slot reduction block would be
+// half empty and nothing is saved; from 64 on the kernels keep the SP/2 = HP rows s < HP and hold every token's slots as two sets of HP/16
+// accumulator tiles: main (slot s of row s) and mirror (slot S - s of row s).  Row 0 has no
+// partner.  When S == SP, slot S/2 would be row HP: its matrix row is A[HP] alone (B is zero
+// there), and since B[0] is zero too, it takes row 0's place in the second set: q_0 is its score
+// and the mirror entry of row 0 its weight ("last row").  Otherwise that mirror entry is unused.
+__host__ __device__ constexpr bool slots_folded(int SP) { return SP >= 64; }
+__host__ __device__ constexpr int slot_rows(int SP) { return slots_folded(SP) ? SP / 2 : SP; }
+
+// Slot held by folded entry i of 0 .. SP-1 (main entries 0 .. HP-1, then mirror entries), or -1.
+__host__ __device__ inline int folded_slot(int i, int S, int SP)
+{
+    const int HP = SP / 2;
+    if (i < HP) return 2 * i <= S && i < S ? i : -1;
+    const int s = i - HP;
+    if (s == 0) return S == SP ? HP : -1;
+    return 2 * s < S ? S - s : -1;
+}
+
+// Start-mask threshold of entry i of the kernels' slot order (folded or natural), from the
+// head's natural thresholds; INT32_MAX for an entry without a slot.
+template <int SP> __device__ __forceinline__ int slot_threshold(const int* theta, int i, int S)
+{
+    if constexpr (slots_folded(SP)) {
+        const int s = folded_slot(i, S, SP);
+        return s < 0 ? INT32_MAX : theta[s];
+    } else {
+        return theta[i];
+    }
+}
+
+// (p, q) -> (main, mirror) scores of the lane's rows 16 i + 4 g + e.
+template <int NHT> __device__ __forceinline__ void fold_scores(floatx4 (&p)[NHT], floatx4 (&q)[NHT], int g)
+{
+#pragma unroll
+    for (int i = 0; i < NHT; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float x = p[i][e], y = q[i][e];
+            const bool row0 = i == 0 && e == 0 && g == 0;
+            p[i][e] = row0 ? x : x + y;
+            q[i][e] = row0 ? y : x - y;
+        }
+}
+
+// (main, mirror) weights -> the weights of A and of B (the last row's in row 0 of B's).  The
+// same map takes score gradients to the gradients of p and q.
+template <int NHT> __device__ __forceinline__ void fold_weights(floatx4 (&p)[NHT], floatx4 (&q)[NHT], int g)
+{
+    fold_scores<NHT>(p, q, g);
+}
+
 // cos and sin of the absolute phase m w P (w = 2 pi / T) for the anchored slots of
 // Sec. 3.3, from the reciprocal period rT = 1 / T.  m P is an exact integer in double;
 // the revolutions m P / T are reduced to [0, 1) in double before the single-precision

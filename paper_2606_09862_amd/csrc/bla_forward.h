@@ -109,10 +109,16 @@ template <typename T, int D, int MP, int SP, int CC = kChunk> struct Fwd : Geo<T
     using G = Geo<T, D, MP, CC>;
     static constexpr int NST = SP / 16;
     static constexpr int KBS = SP / 32;
+    // Slot rows of the tables that the kernel reads (bla_device.h, slot folding), their tiles
+    // and reduction blocks; folded tables also hold the last row, as row HP of ABs and column
+    // HP of ABm (in the row padding).
+    static constexpr bool FOLD = slots_folded(SP);
+    static constexpr int HP = slot_rows(SP), NHT = HP / 16, KBH = HP / 32;
+    static constexpr int ABROWS = FOLD ? HP + 1 : SP, ABCOLS = FOLD ? HP + G::PAD : SP;
     static constexpr int LDG = G::C + G::PAD;    // GT:   [C tokens][LDG]
     static constexpr int LDU = 2 * MP + G::PAD;  // UT:   [C tokens][LDU]
-    static constexpr int LDAS = 2 * MP + G::PAD; // ABs:  [SP][LDAS]
-    static constexpr int LDAM = SP + G::PAD;     // ABm:  [2MP][LDAM]
+    static constexpr int LDAS = 2 * MP + G::PAD; // ABs:  [ABROWS][LDAS]
+    static constexpr int LDAM = HP + G::PAD;     // ABm:  [2MP][LDAM]
     static constexpr int LDE = 2 * MP + G::PAD;  // Etab: [C][LDE]  (also the phase twiddles)
     static constexpr int LDR = G::C + G::PAD;    // EbarT, ErevT: [2MP][LDR]
     // Qs (read in phase A) and UT (written after the next barrier) share one buffer.
@@ -120,7 +126,7 @@ template <typename T, int D, int MP, int SP, int CC = kChunk> struct Fwd : Geo<T
     // ... + the anchored twiddle row [2MP] of the chunk
     static constexpr size_t BASE_ELEMS = 2 * G::KT_ELEMS + (size_t)G::C * LDQU + (size_t)G::C * LDG +
                                          (size_t)D * G::LDZ + (size_t)2 * MP;
-    static constexpr size_t TAB_ELEMS = (size_t)SP * LDAS + (size_t)2 * MP * LDAM + (size_t)G::C * LDE +
+    static constexpr size_t TAB_ELEMS = (size_t)ABROWS * LDAS + (size_t)2 * MP * LDAM + (size_t)G::C * LDE +
                                         (size_t)2 * 2 * MP * LDR;
     // float32 rows rho and rho^C, then the int32 mask thresholds
     static constexpr size_t SMALL_BYTES = (size_t)3 * 2 * MP * 4 + (size_t)SP * 4;
@@ -136,8 +142,11 @@ template <typename T, int D, int MP, int SP, int CC = kChunk> struct Fwd : Geo<T
     static constexpr int LDP = SP + G::PAD;
     static constexpr size_t SPLIT_BYTES = (size_t)G::C * LDP * sizeof(T);
     static constexpr bool SPLIT = sizeof(T) == 2 && G::NW == 2 * G::NT && SP % 64 == 0 && !TL &&
-                                  BASE_BYTES + SPLIT_BYTES <= kMaxLds;
-    static constexpr size_t LDS_BYTES = TL ? FULL_BYTES : BASE_BYTES + (SPLIT ? SPLIT_BYTES : 0);
+                                  BASE_BYTES + SPLIT_BYTES + (size_t)SP * 4 + (size_t)MP * sizeof(T) <= kMaxLds;
+    // without LDS tables the folded thresholds still live there, at the end
+    // (and, for the split chain, the last row of A)
+    static constexpr size_t TH_BYTES = FOLD && !TL ? (size_t)SP * 4 + (SPLIT ? (size_t)MP * sizeof(T) : 0) : 0;
+    static constexpr size_t LDS_BYTES = TL ? FULL_BYTES : BASE_BYTES + (SPLIT ? SPLIT_BYTES : 0) + TH_BYTES;
     static_assert(SP % 32 == 0, "slot padding");
 };
 
@@ -230,9 +239,9 @@ __device__ __forceinline__ void stage_store(const Stage<T, D, MP, CC>& st, T* Qs
     }
 }
 
-// A table copied from the workspace into LDS: ROWS x COLS elements of E, source
-// rows contiguous, destination row stride DSTRIDE (COLS * sizeof(E) a multiple of 8).
-template <typename E, int ROWS, int COLS, int DSTRIDE, int NTHR = kThreads> struct TabCopy {
+// A table copied from the workspace into LDS: ROWS x COLS elements of E, source row stride
+// SSTRIDE, destination row stride DSTRIDE (COLS and the strides multiples of 8 bytes).
+template <typename E, int ROWS, int COLS, int DSTRIDE, int NTHR = kThreads, int SSTRIDE = COLS> struct TabCopy {
     static constexpr int PER = 8 / (int)sizeof(E);        // elements per 8-byte piece
     static constexpr int PIECES = ROWS * COLS / PER;
     static constexpr int ITER = (PIECES + NTHR - 1) / NTHR;
@@ -240,7 +249,7 @@ template <typename E, int ROWS, int COLS, int DSTRIDE, int NTHR = kThreads> stru
 
 // Copy up to two tables with every load of the thread in flight before the first
 // store (the copies run once per workgroup, so their latency is paid only once).
-template <typename E, int ROWS, int COLS, int DSTRIDE, int NTHR = kThreads>
+template <typename E, int ROWS, int COLS, int DSTRIDE, int NTHR = kThreads, int SSTRIDE = COLS>
 __device__ __forceinline__ void copy_table(E* dst, const E* src, int tid)
 {
     typedef int intx2 __attribute__((ext_vector_type(2)));
@@ -249,8 +258,14 @@ __device__ __forceinline__ void copy_table(E* dst, const E* src, int tid)
 #pragma unroll
     for (int i = 0; i < TC::ITER; ++i) {
         const int u = tid + i * NTHR;
-        if (TC::PIECES % NTHR == 0 || u < TC::PIECES)
-            buf[i] = reinterpret_cast<const intx2*>(src)[u];
+        if (TC::PIECES % NTHR == 0 || u < TC::PIECES) {
+            if constexpr (SSTRIDE == COLS) {
+                buf[i] = reinterpret_cast<const intx2*>(src)[u];
+            } else {
+                const int rr = u / (COLS / TC::PER), cc = (u % (COLS / TC::PER)) * TC::PER;
+                buf[i] = *reinterpret_cast<const intx2*>(src + (size_t)rr * SSTRIDE + cc);
+            }
+        }
     }
 #pragma unroll
     for (int i = 0; i < TC::ITER; ++i) {
@@ -498,7 +513,7 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdA
     // split chain: P~ rows (then the H tiles) and the per-token (max, sum) of every slot tile
     T* Pw = reinterpret_cast<T*>(lds_raw + P::BASE_BYTES);
     float* sStat = reinterpret_cast<float*>(GT);
-    static_assert(!P::SPLIT || (size_t)C * P::NST * 2 * 4 <= (size_t)C * P::LDG * sizeof(T), "statistics fit");
+    static_assert(!P::SPLIT || (size_t)C * P::NHT * 2 * 4 <= (size_t)C * P::LDG * sizeof(T), "statistics fit");
 
     const int tid = threadIdx.x, g = (tid & 63) >> 4, r = tid & 15;
     const int tid_ = tid, g_ = g, r_ = r;  // the chunk loop re-derives its own copies
@@ -525,6 +540,7 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdA
     const float* rhoL;   // rho^c of the sequence's last chunk (float32, 2MP)
     const int c_last = a.L - (a.nch - 1) * C;  // length of the last chunk (the only short one)
     const int* tTheta;   // start-mask thresholds [SP]
+    const T* tLast = nullptr;  // split chain: the last row of A, scaled as ABs is
     constexpr int sABs = P::TL ? P::LDAS : 2 * MP;
     constexpr int sABm = P::TL ? P::LDAM : SP;
     constexpr int sEtab = P::TL ? P::LDE : 2 * MP;
@@ -541,21 +557,21 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdA
     const T* fTw = (const T*)a.fTw + (size_t)h * C * 2 * MP;
     if constexpr (P::TL) {
         T* lABs = lPh + (size_t)2 * MP;
-        T* lABm = lABs + (size_t)SP * P::LDAS;
+        T* lABm = lABs + (size_t)P::ABROWS * P::LDAS;
         T* lEtab = lABm + (size_t)2 * MP * P::LDAM;
         T* lEbar = lEtab + (size_t)C * P::LDE;
         T* lErev = lEbar + (size_t)2 * MP * P::LDR;
         float* lRho = reinterpret_cast<float*>(lErev + (size_t)2 * MP * P::LDR);
         int* lTheta = reinterpret_cast<int*>(lRho + 6 * MP);
-        copy_table<T, SP, 2 * MP, P::LDAS, GG::NTHR>(lABs, (const T*)a.ABs, tid);
-        copy_table<T, 2 * MP, SP, P::LDAM, GG::NTHR>(lABm, (const T*)a.ABm, tid);
+        copy_table<T, P::ABROWS, 2 * MP, P::LDAS, GG::NTHR>(lABs, (const T*)a.ABs, tid);
+        copy_table<T, 2 * MP, P::ABCOLS, P::LDAM, GG::NTHR, SP>(lABm, (const T*)a.ABm, tid);
         copy_table<T, C, 2 * MP, P::LDE, GG::NTHR>(lEtab, gEtab, tid);
         copy_table<T, 2 * MP, C, P::LDR, GG::NTHR>(lEbar, gEbar, tid);
         copy_table<T, 2 * MP, C, P::LDR, GG::NTHR>(lErev, gErev, tid);
         copy_table<float, 1, 2 * MP, 2 * MP, GG::NTHR>(lRho, E32h + 2 * MP, tid);                    // rho
         copy_table<float, 1, 2 * MP, 2 * MP, GG::NTHR>(lRho + 2 * MP, E32h + (size_t)C * 2 * MP, tid);  // rho^C
         copy_table<float, 1, 2 * MP, 2 * MP, GG::NTHR>(lRho + 4 * MP, E32h + (size_t)c_last * 2 * MP, tid);  // rho^c_last
-        copy_table<int, 1, SP, SP, GG::NTHR>(lTheta, thh, tid);
+        for (int i = tid; i < SP; i += GG::NTHR) lTheta[i] = slot_threshold<SP>(thh, i, a.S);
         tABs = lABs;
         tABm = lABm;
         tEtab = lEtab;
@@ -574,8 +590,20 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdA
         rho1 = E32h + 2 * MP;
         rhoC = E32h + (size_t)C * 2 * MP;
         rhoL = E32h + (size_t)c_last * 2 * MP;
-        tTheta = thh;
+        if constexpr (P::FOLD) {
+            int* lTheta = reinterpret_cast<int*>(lds_raw + P::LDS_BYTES - P::TH_BYTES);
+            for (int i = tid; i < SP; i += GG::NTHR) lTheta[i] = slot_threshold<SP>(thh, i, a.S);
+            if constexpr (P::SPLIT) {
+                T* lLast = reinterpret_cast<T*>(lTheta + SP);
+                for (int i = tid; i < MP; i += GG::NTHR) lLast[i] = tABs[(size_t)P::HP * 2 * MP + i];
+                tLast = lLast;
+            }
+            tTheta = lTheta;  // visible after the chunk loop's first barrier
+        } else {
+            tTheta = thh;
+        }
     }
+    const bool last_row = P::FOLD && a.S == SP;  // slot S/2 in row 0 of the mirror set
 
     // Eight-wave geometry (bf16): the Gram tile's key rows are read transposed from the staged
     // K^T tile instead of being held in registers a chunk ahead.
@@ -837,23 +865,27 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdA
         // ---- per-token chain, split by output columns over the eight waves
         if constexpr (P::SPLIT) {
             static_assert(NT == 4 && NW == 8 && NMT == NW && NDT == NW, "eight waves, four token tiles");
-            constexpr int NST = P::NST, NTT = NT * NST / NW;  // slot tiles; token tiles per wave
+            constexpr int NHT = P::NHT, NTT = NT * NHT / NW;  // slot-row tiles; token tiles per wave
             const int lane = tid & 63;
             {
-                // (4)-(5) scores of slot tile st for token tiles tt0 .. tt0 + NTT - 1, masked and
-                // exponentiated against the tile's own maximum.  The slot-matrix fragment of
-                // reduction block kb (fragment-ordered: one coalesced 1 KB load) is requested two
-                // blocks ahead and serves every token tile of the wave.
-                const int st = w % NST, tt0 = (w / NST) * NTT;
+                // (4)-(5) scores of slot-row tile st (its slots and their mirror slots) for token
+                // tiles tt0 .. tt0 + NTT - 1, masked and exponentiated against the tile's own
+                // maximum.  The slot-matrix fragment of reduction block kb (fragment-ordered: one
+                // coalesced 1 KB load) is requested two blocks ahead and serves every token tile of
+                // the wave.
+                static_assert(P::FOLD && NTT >= 1, "folded slots");
+                const int st = w % NHT, tt0 = (w / NHT) * NTT;
+                constexpr int KH = GG::KBM / 2;  // reduction blocks of the cosine half
                 F ab[2];
                 auto ld_ab = [&](F& t, int kb) {
                     t = ld_global<F>(fABs + ((size_t)(st * GG::KBM + kb) * 64 + lane) * 8);
                 };
-                floatx4 sc[NTT];
+                floatx4 sc[2][NTT];  // the products with A and with B, then the slots and the mirror slots
 #pragma unroll
-                for (int i = 0; i < NTT; ++i) sc[i] = zero4();
+                for (int i = 0; i < NTT; ++i) sc[0][i] = sc[1][i] = zero4();
                 ld_ab(ab[0], 0);
                 ld_ab(ab[1], 1);
+                const bool lr = last_row && st == 0;  // the last row's products, in row 0 of B's
 #pragma unroll
                 for (int kb = 0; kb < GG::KBM; ++kb) {
                     F uf[NTT];
@@ -862,12 +894,19 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdA
                         uf[i] = ld_frag16_2x8(UT + (size_t)(16 * (tt0 + i) + r) * P::LDQU, kb, g);
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int i = 0; i < NTT; ++i) sc[i] = mma(ab[kb & 1], uf[i], sc[i]);
+                    for (int i = 0; i < NTT; ++i) sc[kb / KH][i] = mma(ab[kb & 1], uf[i], sc[kb / KH][i]);
+                    if (kb < KH && lr) {
+                        F f = ld_frag16_2x8((const bf16*)tLast, kb, g);
+                        if (r != 0) f = zero_frag<T>();
+#pragma unroll
+                        for (int i = 0; i < NTT; ++i) sc[1][i] = mma(f, uf[i], sc[1][i]);
+                    }
                     __builtin_amdgcn_sched_barrier(0);
                     if (kb + 2 < GG::KBM) ld_ab(ab[kb & 1], kb + 2);
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                const intx4 th = *reinterpret_cast<const intx4*>(tTheta + 16 * st + 4 * g);
+                const intx4 th0 = *reinterpret_cast<const intx4*>(tTheta + 16 * st + 4 * g);
+                const intx4 th1 = *reinterpret_cast<const intx4*>(tTheta + P::HP + 16 * st + 4 * g);
 #pragma unroll
                 for (int i = 0; i < NTT; ++i) {
                     const int j = 16 * (tt0 + i) + r;
@@ -875,44 +914,52 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdA
                     float mx = -INFINITY;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        if (pos < (long long)th[e]) sc[i][e] = -INFINITY;
-                        mx = fmaxf(mx, sc[i][e]);
+                        const float x = sc[0][i][e], y = sc[1][i][e];
+                        const bool row0 = e == 0 && g == 0 && st == 0;
+                        sc[0][i][e] = pos < (long long)th0[e] ? -INFINITY : row0 ? x : x + y;
+                        sc[1][i][e] = pos < (long long)th1[e] ? -INFINITY : row0 ? y : x - y;
+                        mx = fmaxf(mx, fmaxf(sc[0][i][e], sc[1][i][e]));
                     }
                     mx = rows_max(mx);
                     // a slot tile can be fully masked (its weights are then zero); tile 0 holds
                     // slot 0, whose threshold is 0
                     const float mref = mx == -INFINITY ? 0.f : mx;
                     float sum = 0.f;
+                    floatx4 wp, wq;  // weights of A and of B
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const float ex = __expf(sc[i][e] - mref);
-                        sc[i][e] = ex;
-                        sum += ex;
+                        const float x = __expf(sc[0][i][e] - mref), y = __expf(sc[1][i][e] - mref);
+                        const bool row0 = e == 0 && g == 0 && st == 0;
+                        wp[e] = row0 ? x : x + y;
+                        wq[e] = row0 ? y : x - y;
+                        sum += x + y;
                     }
                     sum = rows_sum(sum);
-                    st4<T>(Pw + (size_t)j * P::LDP + 16 * st + 4 * g, sc[i]);
+                    st4<T>(Pw + (size_t)j * P::LDP + 16 * st + 4 * g, wp);
+                    st4<T>(Pw + (size_t)j * P::LDP + P::HP + 16 * st + 4 * g, wq);
                     if (g == 0) {
-                        sStat[(j * NST + st) * 2 + 0] = mx;
-                        sStat[(j * NST + st) * 2 + 1] = sum;
+                        sStat[(j * NHT + st) * 2 + 0] = mx;
+                        sStat[(j * NHT + st) * 2 + 1] = sum;
                     }
                 }
             }
             __syncthreads();  // P~ and the statistics visible; U no longer read
             {
                 // (5) normalisation in place: wave w rescales the P~ rows of tokens 8w .. 8w + 7,
-                // eight lanes per token, each lane SP/8 consecutive slots (within one slot tile):
-                // P = P~ exp(m_tile - M) / sum_tiles exp(m_tile - M) s_tile, M the token's maximum
-                constexpr int SPL = SP / 8;  // slots per lane
-                static_assert(SPL == 8 || SPL == 16, "a lane's slots lie in one slot tile");
+                // eight lanes per token, each lane SP/8 consecutive weights (within one slot-row tile
+                // of A's or B's): P = P~ exp(m_tile - M) / sum_tiles exp(m_tile - M) s_tile, M the
+                // token's maximum
+                constexpr int SPL = SP / 8;  // weights per lane
+                static_assert(SPL == 8 || SPL == 16, "a lane's weights lie in one slot-row tile");
                 const int jn = 8 * w + (lane >> 3), s0 = SPL * (lane & 7);
                 float M = -INFINITY, mine = 0.f, tot = 0.f;
 #pragma unroll
-                for (int q = 0; q < NST; ++q) M = fmaxf(M, sStat[(jn * NST + q) * 2]);
+                for (int q = 0; q < NHT; ++q) M = fmaxf(M, sStat[(jn * NHT + q) * 2]);
 #pragma unroll
-                for (int q = 0; q < NST; ++q) {
-                    const float e = __expf(sStat[(jn * NST + q) * 2] - M);  // 0 for a fully masked tile
-                    tot += e * sStat[(jn * NST + q) * 2 + 1];
-                    if (q == s0 / 16) mine = e;
+                for (int q = 0; q < NHT; ++q) {
+                    const float e = __expf(sStat[(jn * NHT + q) * 2] - M);  // 0 for a fully masked tile
+                    tot += e * sStat[(jn * NHT + q) * 2 + 1];
+                    if (q == (s0 % P::HP) / 16) mine = e;
                 }
                 const float f = mine * __builtin_amdgcn_rcpf(tot);
                 T* prow = Pw + (size_t)jn * P::LDP + s0;
@@ -928,16 +975,21 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdA
                 // (6)-(7) readout weights of mode tile w ([Re | Im] column tiles w, NMT + w) for
                 // every token tile; the transposed slot-matrix fragments (fragment-ordered) are
                 // loaded once and serve all four token tiles
-                F am[2][P::KBS];
+                F am[2][P::KBH];  // A from the weights of A, B from those of B
 #pragma unroll
                 for (int pp = 0; pp < 2; ++pp)
 #pragma unroll
-                    for (int ks = 0; ks < P::KBS; ++ks)
+                    for (int ks = 0; ks < P::KBH; ++ks)
                         am[pp][ks] = ld_global<F>(fABm + ((size_t)((pp * NMT + w) * P::KBS + ks) * 64 + lane) * 8);
+                F fl = zero_frag<T>();  // the last row, against row 0 of B's weights
+                if (last_row) {
+                    const T x = ld_global<T>(tABm + (size_t)(16 * w + r) * SP + P::HP);
+                    fl[0] = g == 0 ? x : (T)0.f;
+                }
 #pragma unroll
                 for (int tt = 0; tt < NT; ++tt) {
                     const int j = 16 * tt + r;
-                    F pf[P::KBS];
+                    F pf[P::KBS];  // A's weights, then B's
 #pragma unroll
                     for (int ks = 0; ks < P::KBS; ++ks) pf[ks] = ld_frag16_2x8(Pw + (size_t)j * P::LDP, ks, g);
                     floatx4 wa[2];
@@ -945,8 +997,9 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdA
                     for (int pp = 0; pp < 2; ++pp) {
                         wa[pp] = zero4();
 #pragma unroll
-                        for (int ks = 0; ks < P::KBS; ++ks) wa[pp] = mma(am[pp][ks], pf[ks], wa[pp]);
+                        for (int ks = 0; ks < P::KBH; ++ks) wa[pp] = mma(am[pp][ks], pf[pp * P::KBH + ks], wa[pp]);
                     }
+                    if (last_row) wa[0] = mma(fl, pf[P::KBH], wa[0]);
                     floatx4 cs, sn;
                     if constexpr (AN) {
                         cs = to_f4(ld4_lds<T>(lPh + 16 * w + 4 * g));
@@ -1033,13 +1086,42 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdA
             F uf[GG::KBM];
 #pragma unroll
             for (int kb = 0; kb < GG::KBM; ++kb) uf[kb] = ld_frag<T>(UT + (size_t)j * P::LDQU, 32 * kb, g);
+            // sc: the slots of row tiles 0 .. NHT-1, then (folded) their mirror slots
             floatx4 sc[P::NST];
+            if constexpr (P::FOLD) {
+                constexpr int KH = GG::KBM / 2;  // reduction blocks of the cosine half
+                floatx4 sp[P::NHT], sq[P::NHT];
 #pragma unroll
-            for (int s4 = 0; s4 < P::NST; ++s4) {
-                sc[s4] = zero4();
+                for (int s4 = 0; s4 < P::NHT; ++s4) {
+                    const T* row = tABs + (size_t)(16 * s4 + r) * sABs;
+                    sp[s4] = sq[s4] = zero4();
 #pragma unroll
-                for (int kb = 0; kb < GG::KBM; ++kb)
-                    sc[s4] = mma(ld_frag<T>(tABs + (size_t)(16 * s4 + r) * sABs, 32 * kb, g), uf[kb], sc[s4]);
+                    for (int kb = 0; kb < KH; ++kb) {
+                        sp[s4] = mma(ld_frag<T>(row, 32 * kb, g), uf[kb], sp[s4]);
+                        sq[s4] = mma(ld_frag<T>(row + MP, 32 * kb, g), uf[KH + kb], sq[s4]);
+                    }
+                }
+                if (last_row) {
+#pragma unroll
+                    for (int kb = 0; kb < KH; ++kb) {
+                        const F f = ld_frag<T>(tABs + (size_t)P::HP * sABs, 32 * kb, g);
+                        sq[0] = mma(r == 0 ? f : zero_frag<T>(), uf[kb], sq[0]);
+                    }
+                }
+                fold_scores<P::NHT>(sp, sq, g);
+#pragma unroll
+                for (int s4 = 0; s4 < P::NHT; ++s4) {
+                    sc[s4] = sp[s4];
+                    sc[P::NHT + s4] = sq[s4];
+                }
+            } else {
+#pragma unroll
+                for (int s4 = 0; s4 < P::NST; ++s4) {
+                    sc[s4] = zero4();
+#pragma unroll
+                    for (int kb = 0; kb < GG::KBM; ++kb)
+                        sc[s4] = mma(ld_frag<T>(tABs + (size_t)(16 * s4 + r) * sABs, 32 * kb, g), uf[kb], sc[s4]);
+                }
             }
             float mx = -INFINITY;
 #pragma unroll
@@ -1063,9 +1145,26 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdA
                 }
             sum = rows_sum(sum);
             const float inv = __builtin_amdgcn_rcpf(sum);  // sum >= 1: the maximum slot contributes exp(0)
-            F pf[P::KBS];
+            // slot weights: of A in pf[0], of B in pf[NPW - 1] (the same ones when not folded)
+            constexpr int NPW = P::FOLD ? 2 : 1, KBW = P::FOLD ? P::KBH : P::KBS;
+            F pf[NPW][KBW];
+            if constexpr (P::FOLD) {
+                floatx4 ep[P::NHT], eq[P::NHT];
 #pragma unroll
-            for (int kb = 0; kb < P::KBS; ++kb) pf[kb] = frag_from_acc<T>(sc[2 * kb] * inv, sc[2 * kb + 1] * inv);
+                for (int s4 = 0; s4 < P::NHT; ++s4) {
+                    ep[s4] = sc[s4] * inv;
+                    eq[s4] = sc[P::NHT + s4] * inv;
+                }
+                fold_weights<P::NHT>(ep, eq, g);
+#pragma unroll
+                for (int kb = 0; kb < KBW; ++kb) {
+                    pf[0][kb] = frag_from_acc<T>(ep[2 * kb], ep[2 * kb + 1]);
+                    pf[NPW - 1][kb] = frag_from_acc<T>(eq[2 * kb], eq[2 * kb + 1]);
+                }
+            } else {
+#pragma unroll
+                for (int kb = 0; kb < KBW; ++kb) pf[0][kb] = frag_from_acc<T>(sc[2 * kb] * inv, sc[2 * kb + 1] * inv);
+            }
 
             // W'' by groups of MG mode tiles: the Re and Im tiles of a group are produced,
             // twiddled and packed into their fragments together, so that only 2 MG accumulator
@@ -1085,9 +1184,19 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdA
                         const int t = p * NMT + MG * kb + u;
                         wa[p][u] = zero4();
 #pragma unroll
-                        for (int ks = 0; ks < P::KBS; ++ks)
-                            wa[p][u] = mma(ld_frag<T>(tABm + (size_t)(16 * t + r) * sABm, 32 * ks, g), pf[ks], wa[p][u]);
+                        for (int ks = 0; ks < KBW; ++ks)
+                            wa[p][u] = mma(ld_frag<T>(tABm + (size_t)(16 * t + r) * sABm, 32 * ks, g),
+                                           pf[p * (NPW - 1)][ks], wa[p][u]);
                     }
+                if (last_row) {
+#pragma unroll
+                    for (int u = 0; u < MG; ++u) {
+                        F f = zero_frag<T>();
+                        const T x = tABm[(size_t)(16 * (MG * kb + u) + r) * sABm + P::HP];
+                        f[0] = g == 0 ? x : (T)0.f;
+                        wa[0][u] = mma(f, pf[NPW - 1][0], wa[0][u]);
+                    }
+                }
 #pragma unroll
                 for (int u = 0; u < MG; ++u) {
                     const int mt = MG * kb + u;

@@ -56,6 +56,10 @@ template <int D, int MP, int SP> struct Pair {
     static constexpr int NMT = MP / 16, NDT = D / 16, NST = SP / 16;
     static constexpr int KBD = D / 32, KBM = 2 * MP / 32, KBC = C / 32, KBS = SP / 32;
     static constexpr int OWN = (NMT + WPU - 1) / WPU;
+    // Slot rows held in LDS (bla_device.h, slot folding), their tiles and reduction blocks
+    static constexpr bool FOLD = slots_folded(SP);
+    static constexpr int HP = slot_rows(SP), NHT = HP / 16, KBH = HP / 32;
+    static constexpr int ABROWS = FOLD ? HP + 1 : SP;  // with the last row
     // Row strides (elements): every row is 16 elements longer than its data, i.e. the stride
     // is 8 (mod 32) dwords.  With that stride a 16-lane group's 16-byte row-fragment reads
     // (16 rows, same columns) and its transposed reads (4 rows x 32 bytes) both run at the
@@ -71,14 +75,14 @@ template <int D, int MP, int SP> struct Pair {
     // fragments; Z'_v, read against accumulator-derived fragments, is stored fragment-ordered
     // (frag_col) under the same swizzle, so its fragments are 16-byte reads as well
     // (ld_frag16_sw4 for both, without conflicts).
-    static constexpr int LAB = 2 * MP + 16;  // [A|B]:     [SP][LAB]
+    static constexpr int LAB = 2 * MP + 16;  // [A|B]:     [ABROWS][LAB]
     static constexpr int LE = 2 * MP + 16;   // phase tab: [C][LE]
     static constexpr int LK = D + 16;        // K, V:      [C][LK]
     static constexpr int LZK = D + 16;       // Z'_k:      [2MP][LZK]  (Re rows, then Im rows)
     static constexpr int LZ = 2 * MP + 16;   // Z'_v:      [D][LZ]     (Re | Im along the row, fragment-ordered)
     // per unit, after Z'_v: the anchored twiddle row [cos | sin](m w P) of the chunk, [2MP]
     // (the queries do not pass through LDS: each lane loads its own token's fragments)
-    static constexpr size_t AB_ELEMS = (size_t)SP * LAB;
+    static constexpr size_t AB_ELEMS = (size_t)ABROWS * LAB;
     static constexpr size_t E_ELEMS = (size_t)C * LE;
     static constexpr size_t SHARED_BYTES = 2 * (AB_ELEMS + E_ELEMS) + 3 * 2 * MP * 4 + SP * 4;
     static constexpr size_t UNIT_ELEMS =
@@ -737,7 +741,7 @@ __global__ __launch_bounds__((256 * Pair<D, MP, SP>::U)) void forward_pair_kerne
 
     const float* E32h = a.E32 + (size_t)h * (C + 1) * 2 * MP;
     // ---- shared tables
-    pair_copy<SP, 2 * MP, P::LAB, 256 * P::U, false, true>(sAB, (const bf16*)a.ABs, tid);
+    pair_copy<P::ABROWS, 2 * MP, P::LAB, 256 * P::U, false, true>(sAB, (const bf16*)a.ABs, tid);
     pair_copy<C, 2 * MP, P::LE, 256 * P::U, false, true>(sE, (const bf16*)a.Etab + (size_t)h * C * 2 * MP, tid);
     const int c_last = a.L - (a.nch - 1) * C;
     for (int i = tid; i < 2 * MP; i += 256 * P::U) {
@@ -745,7 +749,8 @@ __global__ __launch_bounds__((256 * Pair<D, MP, SP>::U)) void forward_pair_kerne
         sRho[2 * MP + i] = E32h[(size_t)C * 2 * MP + i];
         sRho[4 * MP + i] = E32h[(size_t)c_last * 2 * MP + i];
     }
-    for (int i = tid; i < SP; i += 256 * P::U) sTheta[i] = a.theta[(size_t)h * SP + i];
+    for (int i = tid; i < SP; i += 256 * P::U) sTheta[i] = slot_threshold<SP>(a.theta + (size_t)h * SP, i, a.S);
+    const bool last_row = P::FOLD && a.S == SP;  // slot S/2 in row 0 of the mirror set
 
     const int ch0 = seg * a.cps;
     const int nch = active ? min(a.cps, a.nch - ch0) : 0;
@@ -993,20 +998,52 @@ __global__ __launch_bounds__((256 * Pair<D, MP, SP>::U)) void forward_pair_kerne
             // (4) scores against the slot matrix (unscaled in LDS)
             const long long pos_ll = a.t0 + tok0 + j;
             const int pos = pos_ll < (1ll << 30) ? (int)pos_ll : (1 << 30);  // every threshold is below 2^30
+            // sc: the slots of row tiles 0 .. NHT-1, then (folded) their mirror slots
             floatx4 sc[P::NST];
+            if constexpr (P::FOLD) {
+                constexpr int KH = P::KBM / 2;  // reduction blocks of the cosine half
+                floatx4 sp[P::NHT], sq[P::NHT];
 #pragma unroll
-            for (int s4 = 0; s4 < P::NST; ++s4) {
-                sc[s4] = zero4();
+                for (int s4 = 0; s4 < P::NHT; ++s4) {
+                    const bf16* row = sAB + (size_t)(16 * s4 + r) * P::LAB;
+                    sp[s4] = sq[s4] = zero4();
 #pragma unroll
-                for (int kb = 0; kb < P::KBM; ++kb)
-                    sc[s4] = mma(ld_frag_2x8_sw(sAB + (size_t)(16 * s4 + r) * P::LAB, kb, g, r), uf[kb], sc[s4]);
+                    for (int kb = 0; kb < KH; ++kb) {
+                        sp[s4] = mma(ld_frag_2x8_sw(row, kb, g, r), uf[kb], sp[s4]);
+                        sq[s4] = mma(ld_frag_2x8_sw(row, KH + kb, g, r), uf[KH + kb], sq[s4]);
+                    }
+                }
+                if (last_row) {
+#pragma unroll
+                    for (int kb = 0; kb < KH; ++kb) {
+                        const F f = ld_frag_2x8(sAB + (size_t)P::HP * P::LAB, kb, g);
+                        sq[0] = mma(r == 0 ? f : zero_frag<bf16>(), uf[kb], sq[0]);
+                    }
+                }
+                fold_scores<P::NHT>(sp, sq, g);
+#pragma unroll
+                for (int s4 = 0; s4 < P::NHT; ++s4) {
+                    sc[s4] = sp[s4];
+                    sc[P::NHT + s4] = sq[s4];
+                }
+            } else {
+#pragma unroll
+                for (int s4 = 0; s4 < P::NST; ++s4) {
+                    sc[s4] = zero4();
+#pragma unroll
+                    for (int kb = 0; kb < P::KBM; ++kb)
+                        sc[s4] = mma(ld_frag_2x8_sw(sAB + (size_t)(16 * s4 + r) * P::LAB, kb, g, r), uf[kb], sc[s4]);
+                }
             }
             // (5) masked softmax in base-2 units (z * scale * log2 e).  Thresholds grow with
-            // the slot and padded slots carry INT32_MAX, so a chunk whose first position
-            // reaches the last threshold needs no mask.
+            // the slot and entries without a slot carry INT32_MAX, so a chunk whose first position
+            // reaches the last slot's threshold needs no mask.  Folded: slot S - 1 is the mirror of
+            // row 1, and with S = SP - 1 only the mirror entry of row 0 has no slot.
             const float k2 = a.scale * 1.44269504088896341f;
             float sum = 0.f;
-            if (k2 > 0.f && a.t0 + tok0 >= (long long)sTheta[SP - 1]) {
+            constexpr int last = P::FOLD ? P::HP + 1 : SP - 1;
+            if (k2 > 0.f && (!P::FOLD || a.S >= SP - 1) && a.t0 + tok0 >= (long long)sTheta[last]) {
+                if constexpr (P::FOLD) sc[P::NHT][0] = g == 0 && !last_row ? -INFINITY : sc[P::NHT][0];
                 // no slot masked and a positive scale: the maximum of the raw scores, and the
                 // scale folded into the exponent's argument, exp2(k2 z - k2 max z)
                 float mx = -INFINITY;
@@ -1046,17 +1083,48 @@ __global__ __launch_bounds__((256 * Pair<D, MP, SP>::U)) void forward_pair_kerne
             }
             sum = rows_sum(sum);
             const float inv = __builtin_amdgcn_rcpf(sum);  // sum >= 1: the maximum slot contributes exp(0)
-            F pf[P::KBS];
-#pragma unroll
-            for (int kb = 0; kb < P::KBS; ++kb) pf[kb] = frag_from_acc<bf16>(sc[2 * kb] * inv, sc[2 * kb + 1] * inv);
-
             // (6) [a | b] = P [A | B], the slot matrix read transposed
             floatx4 wa[2 * NMT];
+            if constexpr (P::FOLD) {
+                floatx4 ep[P::NHT], eq[P::NHT];
 #pragma unroll
-            for (int t = 0; t < 2 * NMT; ++t) {
-                wa[t] = zero4();
+                for (int s4 = 0; s4 < P::NHT; ++s4) {
+                    ep[s4] = sc[s4] * inv;
+                    eq[s4] = sc[P::NHT + s4] * inv;
+                }
+                fold_weights<P::NHT>(ep, eq, g);
+                F pf[P::KBH], qw[P::KBH];
 #pragma unroll
-                for (int kb = 0; kb < P::KBS; ++kb) wa[t] = mma(ld_frag_tr_sw(sAB, P::LAB, 16 * t, kb, g, r), pf[kb], wa[t]);
+                for (int kb = 0; kb < P::KBH; ++kb) {
+                    pf[kb] = frag_from_acc<bf16>(ep[2 * kb], ep[2 * kb + 1]);
+                    qw[kb] = frag_from_acc<bf16>(eq[2 * kb], eq[2 * kb + 1]);
+                }
+#pragma unroll
+                for (int t = 0; t < 2 * NMT; ++t) {
+                    wa[t] = zero4();
+#pragma unroll
+                    for (int kb = 0; kb < P::KBH; ++kb)
+                        wa[t] = mma(ld_frag_tr_sw(sAB, P::LAB, 16 * t, kb, g, r), t < NMT ? pf[kb] : qw[kb], wa[t]);
+                }
+                if (last_row) {
+#pragma unroll
+                    for (int t = 0; t < NMT; ++t) {
+                        F f = zero_frag<bf16>();
+                        const bf16 x = sAB[(size_t)P::HP * P::LAB + 16 * t + r];
+                        f[0] = g == 0 ? x : (bf16)0.f;
+                        wa[t] = mma(f, qw[0], wa[t]);
+                    }
+                }
+            } else {
+                F pf[P::KBS];
+#pragma unroll
+                for (int kb = 0; kb < P::KBS; ++kb) pf[kb] = frag_from_acc<bf16>(sc[2 * kb] * inv, sc[2 * kb + 1] * inv);
+#pragma unroll
+                for (int t = 0; t < 2 * NMT; ++t) {
+                    wa[t] = zero4();
+#pragma unroll
+                    for (int kb = 0; kb < P::KBS; ++kb) wa[t] = mma(ld_frag_tr_sw(sAB, P::LAB, 16 * t, kb, g, r), pf[kb], wa[t]);
+                }
             }
             // (7) [Re W'' | -Im W''] with W'' = (a - i b) o E  (anchored: (a + i b) o conj(rho^P)):
             //     (a, b) <- (a c - b n, b c + a n)

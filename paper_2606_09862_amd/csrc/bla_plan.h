@@ -113,7 +113,7 @@ struct FwdArgs {
     float* carry;
     const float* rotblk;
     const double* rperiod;  // [H] 1 / T (anchored readout only)
-    int B, H, L, M;
+    int B, H, L, M, S;
     int C;        // tokens per chunk (the per-head phase table E32 has C + 1 rows)
     int nch, nseg, cps, cpb, nbs;
     int entered;  // pair kernel: summary slot g - 1 holds the state entering segment g
