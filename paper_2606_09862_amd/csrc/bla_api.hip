@@ -160,6 +160,14 @@ void make_plan_for(const bla_params* p, bool step, bool one_per_cu, Plan* pl)
         const long long target = (long long)cus * (one_per_cu ? 1 : pl->upw);  // units that fill every CU once
         if (units < target) {
             long long want = (target + units - 1) / units;
+            // A scan over the segments takes about 0.125 us each and a chunk of a segment 6.8 us
+            // (d = M = 64): with few sequences, no more segments than balance the two
+            // (4 sequences of 8192 tokens: 128 -> 64 segments,
+            // 58 -> 48 us; one of 16384: 256 -> 86, 74 -> 48 us).
+            if (pl->pair && pl->nch > kMaxPassChunks) {
+                const long long most = (long long)sqrt(54.0 * pl->nch);
+                if (want > most) want = most;
+            }
             int nseg = (int)(want < pl->nch ? want : pl->nch);
             int cps = (pl->nch + nseg - 1) / nseg;
             nseg = (pl->nch + cps - 1) / cps;
