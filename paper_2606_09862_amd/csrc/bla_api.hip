@@ -895,6 +895,7 @@ static bla_status backward_impl(const bla_params* p, const double* T, const void
     a.H = p->H;
     a.L = p->L;
     a.M = p->M;
+    a.S = p->S;
     a.nch = pl.nch;
     a.nseg = bp.nseg;
     a.cps = bp.cps;

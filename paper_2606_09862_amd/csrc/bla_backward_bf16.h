@@ -23,48 +23,65 @@
 namespace bla {
 
 template <int D, int MP, int SP> struct Bwd16 {
-    static constexpr int C = kChunk, NT = C / 16, NW = kThreads / 64;
+    static constexpr int C = kChunk, NT = C / 16, NTHR = 512, NWS = 4;  // eight waves: two sides of four
     static constexpr int NMT = MP / 16, NDT = D / 16, NST = SP / 16;
     static constexpr int KBD = D / 32, KBM = 2 * MP / 32, KBC = C / 32, KBS = SP / 32;
-    static constexpr int OWN = (NMT + NW - 1) / NW;   // mode tiles of the forward state per wave
-    static constexpr int ODT = (NDT + NW - 1) / NW;   // head-dim tiles of the adjoint per wave
+    // slot rows held in LDS (bla_device.h, slot folding)
+    static constexpr bool FOLD = slots_folded(SP);
+    static constexpr int HP = slot_rows(SP), NHT = HP / 16, KBH = HP / 32, ABROWS = FOLD ? HP + 1 : SP;
+    // waves of a side that share a mode tile (they split its token tiles) and a head-dim tile
+    // (they split its keys)
+    static constexpr int NRM = NWS / NMT, NRD = NWS / NDT;
     static constexpr int LDQ = D + 12;                // token tiles [C][LDQ] (read both ways)
     static constexpr int LDK = C + 4;                 // Gram tiles [C][LDK]
-    static constexpr int LDU = 2 * MP + 4;            // U, Y [C][LDU]
-    static constexpr int LE = 2 * MP + 12;            // phase table [C][LE]; slot matrix [SP][LE]
+    static constexpr int LE = 2 * MP + 12;            // phase table [C][LE]; slot matrix [ABROWS][LE]
     // Tiles written row-major by the wave that produces them (8-byte stores) and read
     // transposed (ds_read_b64_tr_b16).  Where the LDS allows it without costing a workgroup
     // per compute unit (PS), they are piece-swizzled (pswz_col) at row strides of 8 x odd
     // (mod 64) dwords, so that neither the stores nor the transposed reads meet bank conflicts;
     // otherwise a stride of 2 (mod 32) dwords keeps the stores conflict-free.
+    static constexpr size_t s_elems() { return ((size_t)ABROWS * LE + 7) / 8 * 8; }
     static constexpr size_t lds_bytes(int tp)
     {
         const int ldh = C + tp, ldw = 2 * MP + tp, ldz = D + tp;
-        return ((size_t)4 * C * LDQ + (size_t)2 * C * (ldh > LDK ? ldh : LDK) +
-                (size_t)2 * C * (ldw > LDU ? ldw : LDU) + (size_t)2 * MP * ldz + (size_t)C * LE + (size_t)SP * LE) * 2 +
+        return ((size_t)4 * C * LDQ + (size_t)2 * C * (ldh > LDK ? ldh : LDK) + (size_t)2 * C * ldw +
+                (size_t)2 * MP * ldz + (size_t)C * LE + s_elems()) * 2 +
                (size_t)SP * 4 + (size_t)2 * 2 * MP * 4;
     }
     static constexpr bool PS =
         lds_bytes(16) <= kBwdMaxLds && (2 * lds_bytes(16) <= kBwdMaxLds || 2 * lds_bytes(4) > kBwdMaxLds);
     static constexpr int TP = PS ? 16 : 4;
     static constexpr int LDH = C + TP;                // H tiles [query][key]
-    static constexpr int LDW = 2 * MP + TP;           // readout weights [token][Re m | Im m]
+    static constexpr int LDW = 2 * MP + TP;           // U, Y, then the readout weights: [token][Re m | Im m]
     static constexpr int LDZ = D + TP;                // Z'_k [Re m | Im m][d]
     __device__ static int tcol(int row, int col) { return PS ? pswz_col(row, col) : col; }
     __device__ static bf16x8 ld_t(const bf16* M, int ld, int x0, int kb, int g, int r)
     {
         return PS ? ld_frag_tr_ps(M, ld, x0, kb, g, r) : ld_frag_tr(M, ld, x0, kb, g, r);
     }
+    // row fragment (accumulator reduction order) of row `row` of such a tile
+    __device__ static bf16x8 ld_row(const bf16* M, int ld, int row, int kb, int g)
+    {
+        const bf16* q = M + (size_t)row * ld + 32 * kb;
+        return join(ld4_lds(q + tcol(row, 4 * g)), ld4_lds(q + 16 + tcol(row, 4 * g)));
+    }
     static constexpr size_t A_ELEMS = (size_t)4 * C * LDQ;
     static constexpr size_t G_ELEMS = (size_t)2 * C * (LDH > LDK ? LDH : LDK);
-    static constexpr size_t B_ELEMS = (size_t)2 * C * (LDW > LDU ? LDW : LDU);
+    static constexpr size_t B_ELEMS = (size_t)2 * C * LDW;
     static constexpr size_t Z_ELEMS = (size_t)2 * MP * LDZ;
     static constexpr size_t E_ELEMS = (size_t)C * LE;
-    static constexpr size_t S_ELEMS = (size_t)SP * LE;
+    static constexpr size_t S_ELEMS = s_elems();
     static constexpr size_t LDS_BYTES =
         (A_ELEMS + G_ELEMS + B_ELEMS + Z_ELEMS + E_ELEMS + S_ELEMS) * 2 + (size_t)SP * 4 + (size_t)2 * 2 * MP * 4;
     static_assert(LDS_BYTES <= kBwdMaxLds, "backward tiles fit in LDS");
     static_assert((size_t)2 * C * LDH <= G_ELEMS, "H tiles fit in the Gram region");
+    // the slot weights handed from one side to the other: four accumulator tiles per query tile in
+    // the Gram region, four more in the query tile's own U rows
+    static_assert((size_t)NT * (NST < 4 ? NST : 4) * 64 * 16 <= G_ELEMS * 2, "slot weights fit in the Gram region");
+    static_assert(NST <= 4 || (size_t)(NST - 4) * 64 * 16 <= (size_t)16 * LDW * 2, "... and in the U rows");
+    // staging: 16-byte pieces of the four token tensors
+    static constexpr int PIECES = 4 * C * D / 8, PPT = PIECES / NTHR;
+    static_assert(PIECES % NTHR == 0 && NMT <= NWS && NDT <= NWS, "tiles split evenly over the waves");
 };
 
 __device__ __forceinline__ bf16x8 neg_frag(bf16x8 f)
@@ -101,12 +118,12 @@ __device__ __forceinline__ void bstage_store_rows(const BStage<bf16, D, NTEN>& s
 
 // The head's phase table as conj(rho^i) = [cos | -sin] rows into LDS ([C][ld]), from the
 // workspace table [C][2MP] of rho^i.
-template <int MP>
+template <int MP, int NTHR = kThreads>
 __device__ __forceinline__ void copy_conj_phase(bf16* dst, int ld, const bf16* src, int tid)
 {
     typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
     constexpr int PIECES = kChunk * 2 * MP / 4;
-    for (int u = tid; u < PIECES; u += kThreads) {
+    for (int u = tid; u < PIECES; u += NTHR) {
         const int row = u / (2 * MP / 4), col = (u % (2 * MP / 4)) * 4;
         u32x2 x = *reinterpret_cast<const u32x2*>(src + (size_t)row * 2 * MP + col);
         if (col >= MP) x ^= 0x80008000u;
@@ -125,10 +142,11 @@ __device__ __forceinline__ const float* rho_row(const float* sRho, int c, int MP
 // the only chunk that can be shorter).  Both rows live in LDS, so the selected row is read
 // with LDS loads (a row chosen between LDS and global memory would be read with flat loads,
 // which hold every LDS wait until they return).
+template <int NTHR = kThreads>
 __device__ __forceinline__ void load_rho_rows(float* sRho, const float* E32h, const BwdArgs& a, int MP, int tid)
 {
     const int c_last = a.L - (a.nch - 1) * kChunk;
-    for (int i = tid; i < 2 * MP; i += kThreads) {
+    for (int i = tid; i < 2 * MP; i += NTHR) {
         sRho[i] = E32h[(size_t)kChunk * 2 * MP + i];
         sRho[2 * MP + i] = E32h[(size_t)c_last * 2 * MP + i];
     }
@@ -141,7 +159,7 @@ template <int D, int MP>
 __global__ __launch_bounds__(kThreads) void bwd16_fsum_kernel(BwdArgs a)
 {
     using G = Bwd16<D, MP, 32>;
-    constexpr int C = kChunk, NMT = G::NMT, NDT = G::NDT, OWN = G::OWN, NW = G::NW;
+    constexpr int C = kChunk, NMT = G::NMT, NDT = G::NDT, NW = kThreads / 64, OWN = (NMT + NW - 1) / NW;
     // K, V and the phase table are read only transposed here: row strides of 8 x odd (mod 64)
     // dwords keep those reads free of bank conflicts
     constexpr int LDQ = D + 16, LE = 2 * MP + 16;
@@ -231,27 +249,36 @@ __global__ __launch_bounds__(kThreads) void bwd16_fsum_kernel(BwdArgs a)
 
 // ---------------------------------------------------------------------------------
 // The reverse walk over one (b, h, segment), bf16.  SUM: adjoint summary only.
+//
+// Eight waves, two per SIMD, in two sides of four.  Side 0 carries what belongs to the keys and
+// queries (Z'_k, its Gram tiles, U, the scores, H_v, Gam'_k, dk), side 1 what belongs to the
+// values (Z'_v, Gd, Y, dP, H_q, Gam'_v, dv): the phases below are the same for both, so a wave
+// holds half of the state and adjoint registers that one wave per SIMD held, and every SIMD has a
+// second chain to issue from while one waits.  Only the softmax crosses over: side 0 hands its
+// weights to side 1 in float32.  dq is shared out over all eight at the end.  (One wave per SIMD
+// took 401 us for the walk and 153 us for the adjoint summaries at 128 sequences of 4096
+// tokens, d = M = S = 64; now 328 and 120.)
 template <int D, int MP, int SP, bool SUM>
-__global__ __launch_bounds__(kThreads) void bwd16_kernel(BwdArgs a)
+__global__ __launch_bounds__((Bwd16<D, MP, SP>::NTHR)) void bwd16_kernel(BwdArgs a)
 {
     using P = Bwd16<D, MP, SP>;
     using F = bf16x8;
-    constexpr int C = P::C, NT = P::NT, NW = P::NW, NMT = P::NMT, NDT = P::NDT, OWN = P::OWN, ODT = P::ODT;
-    constexpr int KBD = P::KBD, KBM = P::KBM, KBC = P::KBC, NST = P::NST, KBS = P::KBS;
-    constexpr int LDQ = P::LDQ, LDK = P::LDK, LDU = P::LDU, LE = P::LE;
+    constexpr int C = P::C, NT = P::NT, NMT = P::NMT, NDT = P::NDT, NTHR = P::NTHR;
+    constexpr int KBD = P::KBD, KBM = P::KBM, KBC = P::KBC, NST = P::NST, NHT = P::NHT;
+    constexpr int LDQ = P::LDQ, LDK = P::LDK, LDW = P::LDW, LE = P::LE;
     __shared__ __attribute__((aligned(16))) char lds_raw[P::LDS_BYTES];
     bf16* Ks = reinterpret_cast<bf16*>(lds_raw);            // region A: token tiles, row-major
     bf16* Vs = Ks + (size_t)C * LDQ;
     bf16* Qs = Vs + (size_t)C * LDQ;
     bf16* dOs = Qs + (size_t)C * LDQ;
-    bf16* GT = Ks + P::A_ELEMS;                              // region G: Gram tiles, then H tiles
+    bf16* GT = Ks + P::A_ELEMS;                              // region G: Gram tiles, slot weights, H tiles
     bf16* GdT = GT + (size_t)C * LDK;
     bf16* HqT = GT;                                          // [query][key], LDH
     bf16* HvT = GT + (size_t)C * P::LDH;
     bf16* UT = GT + P::G_ELEMS;                              // region B: U, Y, then the weights
-    bf16* YT = UT + (size_t)C * LDU;
+    bf16* YT = UT + (size_t)C * LDW;
     bf16* WqT = UT;                                          // [token][Re m | Im m], LDW
-    bf16* WvT = WqT + (size_t)C * P::LDW;
+    bf16* WvT = YT;
     bf16* ZkT = UT + P::B_ELEMS;                             // [Re m | Im m][d] of Z'_k, LDZ
     bf16* sE = ZkT + P::Z_ELEMS;                             // conj(rho^i) rows
     bf16* sAB = sE + P::E_ELEMS;                             // scale (A | B) rows
@@ -260,7 +287,15 @@ __global__ __launch_bounds__(kThreads) void bwd16_kernel(BwdArgs a)
 
     const int tid = threadIdx.x, g = (tid & 63) >> 4, r = tid & 15;
     const int tid_ = tid, g_ = g, r_ = r;  // the chunk loop re-derives its own copies
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int side = wv / P::NWS, w = wv % P::NWS;  // side, and wave within it
+    const int mt = w % NMT, rm = w / NMT;           // mode tile, and which of the waves that share it
+    const int dt = w % NDT, rd = w / NDT;           // head-dim tile, likewise
+    // Token tiles of the waves that share a mode or head-dim tile (causal work grows with the
+    // index: 0, 3 | 1, 2 for two, one each for four).
+    auto mine = [](int t, int part, int parts) {
+        return parts == 1 || (parts == 2 ? ((t == 1 || t == 2) == (part == 1)) : t == part);
+    };
     // SUM: one summary block of a segment but the first; otherwise one segment.  last_blk:
     // the last summary block the walk covers.
     const int bps = a.nbk / a.nseg;
@@ -278,151 +313,124 @@ __global__ __launch_bounds__(kThreads) void bwd16_kernel(BwdArgs a)
     const float* rho1 = E32h + 2 * MP;
     const float iscale = 1.f / a.scale;
 
+    // Staging of one chunk: 16-byte pieces of K, V, Q, dO (rows past c re-read row c - 1 and are
+    // stored as zeros), loaded a chunk ahead.
+    F st[P::PPT];
+    auto stage_load = [&](int tok0, int c, int tid) {
+#pragma unroll
+        for (int i = 0; i < P::PPT; ++i) {
+            // a wave's pieces lie in one tensor: uniform base, 32-bit lane offset
+            const int u0 = 64 * wv + NTHR * i, ten = u0 / (C * D / 8), u = u0 % (C * D / 8) + (tid & 63);
+            const bf16* base = (ten == 0 ? kb_ : ten == 1 ? vb : ten == 2 ? qb : gb) + (size_t)tok0 * D;
+            const int row = min(u / (D / 8), c - 1);
+            st[i] = ld_global<F>(base + (unsigned)(row * D + 8 * (u % (D / 8))));
+        }
+    };
+    auto stage_store = [&](int c, int tid) {
+#pragma unroll
+        for (int i = 0; i < P::PPT; ++i) {
+            const int u0 = 64 * wv + NTHR * i, ten = u0 / (C * D / 8), u = u0 % (C * D / 8) + (tid & 63);
+            const int row = u / (D / 8);
+            const F x = row < c ? st[i] : zero_frag<bf16>();
+            bf16* d = Ks + (size_t)ten * C * LDQ + (size_t)row * LDQ + 8 * (u % (D / 8));
+            st_lds<bf16x4>(d, __builtin_shufflevector(x, x, 0, 1, 2, 3));
+            st_lds<bf16x4>(d + 4, __builtin_shufflevector(x, x, 4, 5, 6, 7));
+        }
+    };
     // first (last in time) chunk's loads go out before the tables are copied
-    BStage<bf16, D, 4> st;
     if (nch > 0) {
         const int tok0 = (ch0 + nch - 1) * C;
-        const bf16* src[4] = {kb_ + (size_t)tok0 * D, vb + (size_t)tok0 * D, qb + (size_t)tok0 * D,
-                              gb + (size_t)tok0 * D};
-        bstage_load<bf16, D, 4>(st, src, min(C, a.L - tok0), tid);
+        stage_load(tok0, min(C, a.L - tok0), tid);
     }
-    copy_conj_phase<MP>(sE, LE, (const bf16*)a.Etab + (size_t)h * C * 2 * MP, tid);
-    copy_table<bf16, SP, 2 * MP, LE>(sAB, (const bf16*)a.ABs, tid);
-    for (int i = tid; i < SP; i += kThreads) sTheta[i] = a.theta[(size_t)h * SP + i];
-    load_rho_rows(sRhoC, E32h, a, MP, tid);
+    copy_conj_phase<MP, NTHR>(sE, LE, (const bf16*)a.Etab + (size_t)h * C * 2 * MP, tid);
+    copy_table<bf16, P::ABROWS, 2 * MP, LE, NTHR>(sAB, (const bf16*)a.ABs, tid);
+    for (int i = tid; i < SP; i += NTHR) sTheta[i] = slot_threshold<SP>(a.theta + (size_t)h * SP, i, a.S);
+    load_rho_rows<NTHR>(sRhoC, E32h, a, MP, tid);
+    const bool last_row = P::FOLD && a.S == SP;  // slot S/2 in row 0 of the mirror set
 
-    // ---- forward state after the segment (pre-rotated, [d][m] tiles, mode tiles split)
-    StateTiles<bf16, D, MP> Zk, Zv;
-#pragma unroll
-    for (int o = 0; o < OWN; ++o) {
-        const int mt = w + NW * o;
+    // ---- forward state after the segment (pre-rotated, [d][m] tiles): side 0 Z'_k, side 1 Z'_v
+    floatx4 Z[2][NDT];
+    {
         const int m = 16 * mt + r;
-        const bool live = mt < NMT;
-        const float c1 = live ? rho1[m] : 0.f, s1 = live ? rho1[MP + m] : 0.f;
+        const float* sin_ = side ? a.sv_in : a.sk_in;
+        const float c1 = rho1[m], s1 = rho1[MP + m];
 #pragma unroll
-        for (int dt = 0; dt < NDT; ++dt) {
-            floatx4 kr = zero4(), ki = zero4(), vr = zero4(), vi = zero4();
-            if (live && m < a.M) {
-                if (a.sk_in) {
-                    kr = ld4f(a.sk_in + (((size_t)bh * 2 + 0) * a.M + m) * D + 16 * dt + 4 * g);
-                    ki = ld4f(a.sk_in + (((size_t)bh * 2 + 1) * a.M + m) * D + 16 * dt + 4 * g);
-                }
-                if (a.sv_in) {
-                    vr = ld4f(a.sv_in + (((size_t)bh * 2 + 0) * a.M + m) * D + 16 * dt + 4 * g);
-                    vi = ld4f(a.sv_in + (((size_t)bh * 2 + 1) * a.M + m) * D + 16 * dt + 4 * g);
-                }
+        for (int d4 = 0; d4 < NDT; ++d4) {
+            floatx4 xr = zero4(), xi = zero4();
+            if (sin_ && m < a.M) {
+                xr = ld4f(sin_ + (((size_t)bh * 2 + 0) * a.M + m) * D + 16 * d4 + 4 * g);
+                xi = ld4f(sin_ + (((size_t)bh * 2 + 1) * a.M + m) * D + 16 * d4 + 4 * g);
             }
-            Zk[o][0][dt] = c1 * kr - s1 * ki;
-            Zk[o][1][dt] = s1 * kr + c1 * ki;
-            Zv[o][0][dt] = c1 * vr - s1 * vi;
-            Zv[o][1][dt] = s1 * vr + c1 * vi;
+            Z[0][d4] = c1 * xr - s1 * xi;
+            Z[1][d4] = s1 * xr + c1 * xi;
         }
-    }
-    for (int sg = 0; sg <= last_blk; ++sg) {
-        const long long len = (long long)min(a.cpb * C, a.L - sg * a.cpb * C);
-        const float* S = a.fsum + ((size_t)bh * a.nbk + sg) * 4 * MP * D;
+        for (int sg = 0; sg <= last_blk; ++sg) {
+            const long long len = (long long)min(a.cpb * C, a.L - sg * a.cpb * C);
+            const float* S = a.fsum + ((size_t)bh * a.nbk + sg) * 4 * MP * D + (size_t)2 * side * MP * D;
+            float cc, ss;
+            bwd_phase(m, len, rT, cc, ss);
 #pragma unroll
-        for (int o = 0; o < OWN; ++o) {
-            const int mt = w + NW * o;
-            if (mt < NMT) {
-                const int m = 16 * mt + r;
-                float cc, ss;
-                bwd_phase(m, len, rT, cc, ss);
-#pragma unroll
-                for (int p2 = 0; p2 < 2; ++p2) {
-                    StateTiles<bf16, D, MP>& Z = p2 ? Zv : Zk;
-#pragma unroll
-                    for (int dt = 0; dt < NDT; ++dt) {
-                        const floatx4 re = Z[o][0][dt], im = Z[o][1][dt];
-                        const floatx4 sr = ld4f(S + ((size_t)(2 * p2 + 0) * MP + m) * D + 16 * dt + 4 * g);
-                        const floatx4 si = ld4f(S + ((size_t)(2 * p2 + 1) * MP + m) * D + 16 * dt + 4 * g);
-                        Z[o][0][dt] = cc * re - ss * im + sr;
-                        Z[o][1][dt] = ss * re + cc * im + si;
-                    }
-                }
+            for (int d4 = 0; d4 < NDT; ++d4) {
+                const floatx4 re = Z[0][d4], im = Z[1][d4];
+                const floatx4 sr = ld4f(S + (size_t)m * D + 16 * d4 + 4 * g);
+                const floatx4 si = ld4f(S + ((size_t)MP + m) * D + 16 * d4 + 4 * g);
+                Z[0][d4] = cc * re - ss * im + sr;
+                Z[1][d4] = ss * re + cc * im + si;
             }
         }
     }
 
-    // ---- adjoint after the segment (pre-rotated, [m][d] tiles; wave w owns d-tile w + NW od for
-    // every mode tile): Horner over the adjoint summaries of the later segments from
-    // rho dLoss/d(final states)
-    floatx4 Gk[ODT][2][NMT], Gv[ODT][2][NMT];
+    // ---- adjoint after the segment (pre-rotated, [m][d] tiles of head-dim tile dt, every mode
+    // tile; side 0 Gam'_k, side 1 Gam'_v): Horner over the adjoint summaries of the later segments
+    // from rho dLoss/d(final states)
+    floatx4 Gm[2][NMT];
+    const float* gout = side ? a.gv_out : a.gk_out;
 #pragma unroll
-    for (int od = 0; od < ODT; ++od) {
-        const int dt = w + NW * od;
-        const bool live = dt < NDT;
+    for (int m4 = 0; m4 < NMT; ++m4) {
+        Gm[0][m4] = Gm[1][m4] = zero4();
+        if (!SUM && gout) {
 #pragma unroll
-        for (int mt = 0; mt < NMT; ++mt) {
-            floatx4 kr = zero4(), ki = zero4(), vr = zero4(), vi = zero4();
-            if (!SUM && live) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int m = 16 * mt + 4 * g + e;
-                    if (m < a.M) {
-                        const float c1 = rho1[m], s1 = rho1[MP + m];
-                        float xr = 0.f, xi = 0.f, yr = 0.f, yi = 0.f;
-                        const size_t o0 = (((size_t)bh * 2 + 0) * a.M + m) * D + 16 * dt + r;
-                        const size_t o1 = (((size_t)bh * 2 + 1) * a.M + m) * D + 16 * dt + r;
-                        if (a.gk_out) {
-                            xr = a.gk_out[o0];
-                            xi = a.gk_out[o1];
-                        }
-                        if (a.gv_out) {
-                            yr = a.gv_out[o0];
-                            yi = a.gv_out[o1];
-                        }
-                        kr[e] = c1 * xr - s1 * xi;
-                        ki[e] = s1 * xr + c1 * xi;
-                        vr[e] = c1 * yr - s1 * yi;
-                        vi[e] = s1 * yr + c1 * yi;
-                    }
+            for (int e = 0; e < 4; ++e) {
+                const int m = 16 * m4 + 4 * g + e;
+                if (m < a.M) {
+                    const float c1 = rho1[m], s1 = rho1[MP + m];
+                    const float xr = gout[(((size_t)bh * 2 + 0) * a.M + m) * D + 16 * dt + r];
+                    const float xi = gout[(((size_t)bh * 2 + 1) * a.M + m) * D + 16 * dt + r];
+                    Gm[0][m4][e] = c1 * xr - s1 * xi;
+                    Gm[1][m4][e] = s1 * xr + c1 * xi;
                 }
             }
-            Gk[od][0][mt] = kr;
-            Gk[od][1][mt] = ki;
-            Gv[od][0][mt] = vr;
-            Gv[od][1][mt] = vi;
         }
     }
     if constexpr (!SUM) {
         for (int sg = a.nbk - 1; sg > last_blk; --sg) {
             const long long len = (long long)min(a.cpb * C, a.L - sg * a.cpb * C);
-            const float* S = a.asum + ((size_t)bh * a.nbk + sg) * 4 * MP * D;
+            const float* S = a.asum + ((size_t)bh * a.nbk + sg) * 4 * MP * D + (size_t)2 * side * MP * D;
 #pragma unroll
-            for (int od = 0; od < ODT; ++od) {
-                const int dt = w + NW * od;
-                if (dt >= NDT) continue;
+            for (int m4 = 0; m4 < NMT; ++m4) {
+                floatx4 cc, ss, sr, si;
 #pragma unroll
-                for (int mt = 0; mt < NMT; ++mt) {
-                    floatx4 cc, ss;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        float ce, se;
-                        bwd_phase(16 * mt + 4 * g + e, len, rT, ce, se);
-                        cc[e] = ce;
-                        ss[e] = se;
-                    }
-#pragma unroll
-                    for (int p2 = 0; p2 < 2; ++p2) {
-                        floatx4(&Gm)[2][NMT] = p2 ? Gv[od] : Gk[od];
-                        floatx4 sr, si;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const int m = 16 * mt + 4 * g + e;
-                            sr[e] = S[((size_t)(2 * p2 + 0) * MP + m) * D + 16 * dt + r];
-                            si[e] = S[((size_t)(2 * p2 + 1) * MP + m) * D + 16 * dt + r];
-                        }
-                        const floatx4 re = Gm[0][mt], im = Gm[1][mt];
-                        Gm[0][mt] = cc * re + ss * im + sr;
-                        Gm[1][mt] = cc * im - ss * re + si;
-                    }
+                for (int e = 0; e < 4; ++e) {
+                    const int m = 16 * m4 + 4 * g + e;
+                    float ce, se;
+                    bwd_phase(m, len, rT, ce, se);
+                    cc[e] = ce;
+                    ss[e] = se;
+                    sr[e] = S[(size_t)m * D + 16 * dt + r];
+                    si[e] = S[((size_t)MP + m) * D + 16 * dt + r];
                 }
+                const floatx4 re = Gm[0][m4], im = Gm[1][m4];
+                Gm[0][m4] = cc * re + ss * im + sr;
+                Gm[1][m4] = cc * im - ss * re + si;
             }
         }
     }
     __syncthreads();  // tables in LDS
 
+    const bf16* Xs = side ? Vs : Ks;      // the side's keys or values ...
+    const bf16* Rs = side ? dOs : Qs;     // ... and what they meet: queries or output gradients
+    bf16* Gs = side ? GdT : GT;
+    bf16* Us = side ? YT : UT;
     for (int n = nch - 1; n >= 0; --n) {
         // lane indices re-derived per chunk (opaque_lane): addresses stay inside the loop
         const int r = opaque_lane(r_), g = opaque_lane(g_), tid = opaque_lane(tid_);
@@ -430,427 +438,377 @@ __global__ __launch_bounds__(kThreads) void bwd16_kernel(BwdArgs a)
         const int c = min(C, a.L - tok0);
         const float* rc = rho_row(sRhoC, c, MP);  // rho^c
         __syncthreads();  // previous chunk done with the token tiles and the weights
-        {
-            bf16* rows[4] = {Ks, Vs, Qs, dOs};
-            bstage_store_rows<D, 4>(st, rows, LDQ, c, tid);
-        }
-        if (n > 0) {
-            const int tp = tok0 - C;
-            const bf16* src[4] = {kb_ + (size_t)tp * D, vb + (size_t)tp * D, qb + (size_t)tp * D, gb + (size_t)tp * D};
-            bstage_load<bf16, D, 4>(st, src, C, tid);
-        }
+        stage_store(c, tid);
+        if (n > 0) stage_load(tok0 - C, C, tid);
         __syncthreads();  // token tiles visible
 
-        // ---- phase 1 (mode tiles): Z'_in = conj(rho^c) o Z'_out - sum_i conj(rho^i) x_i; publish
-        // Z'_k for dq; Gram tiles of key tile w
-        rotate_dm<bf16, D, MP, true>(Zk, rc, w, r);
-        rotate_dm<bf16, D, MP, true>(Zv, rc, w, r);
+        // ---- phase 1: Z'_in = conj(rho^c) o Z'_out - sum_i conj(rho^i) x_i on the wave's mode
+        // tile; Z'_k published for dq; Gram tiles of key tile w
+        {
+            const float cc = rc[16 * mt + r], ss = rc[MP + 16 * mt + r];
+#pragma unroll
+            for (int d4 = 0; d4 < NDT; ++d4) {
+                const floatx4 re = Z[0][d4], im = Z[1][d4];
+                Z[0][d4] = cc * re + ss * im;
+                Z[1][d4] = cc * im - ss * re;
+            }
+        }
 #pragma unroll
         for (int kb = 0; kb < KBC; ++kb) {
-            F kf[NDT], vf[NDT];
+            F ef[2];
 #pragma unroll
-            for (int dt = 0; dt < NDT; ++dt) {
-                kf[dt] = neg_frag(ld_frag_tr(Ks, LDQ, 16 * dt, kb, g, r));
-                vf[dt] = neg_frag(ld_frag_tr(Vs, LDQ, 16 * dt, kb, g, r));
-            }
+            for (int p = 0; p < 2; ++p) ef[p] = neg_frag(ld_frag_tr(sE, LE, p * MP + 16 * mt, kb, g, r));
 #pragma unroll
-            for (int o = 0; o < OWN; ++o) {
-                const int mt = w + NW * o;
-                if (mt >= NMT) continue;
+            for (int d4 = 0; d4 < NDT; ++d4) {
+                const F xf = ld_frag_tr(Xs, LDQ, 16 * d4, kb, g, r);
 #pragma unroll
-                for (int p = 0; p < 2; ++p) {
-                    const F ef = ld_frag_tr(sE, LE, p * MP + 16 * mt, kb, g, r);
-#pragma unroll
-                    for (int dt = 0; dt < NDT; ++dt) {
-                        Zk[o][p][dt] = mma(kf[dt], ef, Zk[o][p][dt]);
-                        Zv[o][p][dt] = mma(vf[dt], ef, Zv[o][p][dt]);
-                    }
-                }
+                for (int p = 0; p < 2; ++p) Z[p][d4] = mma(xf, ef[p], Z[p][d4]);
             }
         }
         if constexpr (!SUM) {
+            if (side == 0 && rm == 0) {
 #pragma unroll
-            for (int o = 0; o < OWN; ++o) {
-                const int mt = w + NW * o;
-                if (mt < NMT) {
+                for (int d4 = 0; d4 < NDT; ++d4)
 #pragma unroll
-                    for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-                        for (int p = 0; p < 2; ++p)
-                            st_lds<bf16x4>(ZkT + (size_t)(p * MP + 16 * mt + r) * P::LDZ + P::tcol(p * MP + 16 * mt + r, 16 * dt + 4 * g),
-                                           cvt4(Zk[o][p][dt], bf16()));
-                }
+                    for (int p = 0; p < 2; ++p) {
+                        const int row = p * MP + 16 * mt + r;
+                        st_lds<bf16x4>(ZkT + (size_t)row * P::LDZ + P::tcol(row, 16 * d4 + 4 * g), cvt4(Z[p][d4], bf16()));
+                    }
             }
         }
         {
-            F kf[KBD], vf[KBD];
+            F xf[KBD];
 #pragma unroll
-            for (int kb = 0; kb < KBD; ++kb) {
-                kf[kb] = ld_frag<bf16>(Ks + (size_t)(16 * w + r) * LDQ, 32 * kb, g);
-                vf[kb] = ld_frag<bf16>(Vs + (size_t)(16 * w + r) * LDQ, 32 * kb, g);
-            }
+            for (int kb = 0; kb < KBD; ++kb) xf[kb] = ld_frag<bf16>(Xs + (size_t)(16 * w + r) * LDQ, 32 * kb, g);
 #pragma unroll
             for (int ct = 0; ct < NT; ++ct) {
                 if (ct < w) continue;
                 const int j = 16 * ct + r;
-                floatx4 ga = zero4(), gd = zero4();
+                floatx4 ga = zero4();
 #pragma unroll
-                for (int kb = 0; kb < KBD; ++kb) {
-                    ga = mma(kf[kb], ld_frag<bf16>(Qs + (size_t)j * LDQ, 32 * kb, g), ga);
-                    gd = mma(vf[kb], ld_frag<bf16>(dOs + (size_t)j * LDQ, 32 * kb, g), gd);
-                }
+                for (int kb = 0; kb < KBD; ++kb) ga = mma(xf[kb], ld_frag<bf16>(Rs + (size_t)j * LDQ, 32 * kb, g), ga);
                 if (ct == w) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        if (4 * g + e > r) ga[e] = gd[e] = 0.f;
+                        if (4 * g + e > r) ga[e] = 0.f;
                 }
-                st4<bf16>(GT + (size_t)j * LDK + 16 * w + 4 * g, ga);
-                st4<bf16>(GdT + (size_t)j * LDK + 16 * w + 4 * g, gd);
+                st_lds<bf16x4>(Gs + (size_t)j * LDK + 16 * w + 4 * g, cvt4(ga, bf16()));
             }
         }
         __syncthreads();  // Gram tiles visible
 
-        // ---- phase 2 (mode tiles): U = E o (Q Z'_k^T + G conj(E)), Y = E o (dO Z'_v^T + Gd conj(E))
+        // ---- phase 2 (mode tile mt): U = E o (Q Z'_k^T + G conj(E)), side 1 Y = E o (dO Z'_v^T + Gd conj(E))
         {
-            F zkf[OWN][2][KBD], zvf[OWN][2][KBD];
+            F zf[2][KBD], ef[KBC][2];
 #pragma unroll
-            for (int o = 0; o < OWN; ++o)
+            for (int p = 0; p < 2; ++p)
 #pragma unroll
-                for (int p = 0; p < 2; ++p)
+                for (int kb = 0; kb < KBD; ++kb) zf[p][kb] = frag_from_acc<bf16>(Z[p][2 * kb], Z[p][2 * kb + 1]);
 #pragma unroll
-                    for (int kb = 0; kb < KBD; ++kb) {
-                        zkf[o][p][kb] = frag_from_acc<bf16>(Zk[o][p][2 * kb], Zk[o][p][2 * kb + 1]);
-                        zvf[o][p][kb] = frag_from_acc<bf16>(Zv[o][p][2 * kb], Zv[o][p][2 * kb + 1]);
-                    }
+            for (int kb = 0; kb < KBC; ++kb)
+#pragma unroll
+                for (int p = 0; p < 2; ++p) ef[kb][p] = ld_frag_tr(sE, LE, p * MP + 16 * mt, kb, g, r);
 #pragma unroll
             for (int ct = 0; ct < NT; ++ct) {
+                if (!mine(ct, rm, P::NRM)) continue;
                 const int j = 16 * ct + r;
-                F qf[KBD], of[KBD];
+                F xf[KBD];
 #pragma unroll
-                for (int kb = 0; kb < KBD; ++kb) {
-                    qf[kb] = ld_frag<bf16>(Qs + (size_t)j * LDQ, 32 * kb, g);
-                    of[kb] = ld_frag<bf16>(dOs + (size_t)j * LDQ, 32 * kb, g);
+                for (int kb = 0; kb < KBD; ++kb) xf[kb] = ld_frag<bf16>(Rs + (size_t)j * LDQ, 32 * kb, g);
+                floatx4 u[2];
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    u[p] = zero4();
+#pragma unroll
+                    for (int kb = 0; kb < KBD; ++kb) u[p] = mma(zf[p][kb], xf[kb], u[p]);
                 }
 #pragma unroll
-                for (int o = 0; o < OWN; ++o) {
-                    const int mt = w + NW * o;
-                    if (mt >= NMT) continue;
-                    floatx4 u[2], y[2];
+                for (int kb = 0; kb < KBC; ++kb) {
+                    if (2 * kb <= ct) {
+                        const bf16* grow = Gs + (size_t)j * LDK;
+                        const F gf = 2 * kb + 1 <= ct ? ld_frag<bf16>(grow, 32 * kb, g) : ld_frag_lo<bf16>(grow, 32 * kb, g);
 #pragma unroll
-                    for (int p = 0; p < 2; ++p) {
-                        u[p] = y[p] = zero4();
-#pragma unroll
-                        for (int kb = 0; kb < KBD; ++kb) {
-                            u[p] = mma(zkf[o][p][kb], qf[kb], u[p]);
-                            y[p] = mma(zvf[o][p][kb], of[kb], y[p]);
-                        }
+                        for (int p = 0; p < 2; ++p) u[p] = mma(ef[kb][p], gf, u[p]);
                     }
-#pragma unroll
-                    for (int kb = 0; kb < KBC; ++kb) {
-                        if (2 * kb <= ct) {
-                            const bf16* grow = GT + (size_t)j * LDK;
-                            const bf16* drow = GdT + (size_t)j * LDK;
-                            const bool full = 2 * kb + 1 <= ct;
-                            const F gf = full ? ld_frag<bf16>(grow, 32 * kb, g) : ld_frag_lo<bf16>(grow, 32 * kb, g);
-                            const F df = full ? ld_frag<bf16>(drow, 32 * kb, g) : ld_frag_lo<bf16>(drow, 32 * kb, g);
-#pragma unroll
-                            for (int p = 0; p < 2; ++p) {
-                                const F ef = ld_frag_tr(sE, LE, p * MP + 16 * mt, kb, g, r);
-                                u[p] = mma(ef, gf, u[p]);
-                                y[p] = mma(ef, df, y[p]);
-                            }
-                        }
-                    }
-                    // E o X with the stored row [c | -s] of token j
-                    const floatx4 cs = to_f4(ld4_lds<bf16>(sE + (size_t)j * LE + 16 * mt + 4 * g));
-                    const floatx4 ns = to_f4(ld4_lds<bf16>(sE + (size_t)j * LE + MP + 16 * mt + 4 * g));
-                    st4<bf16>(UT + (size_t)j * LDU + 16 * mt + 4 * g, cs * u[0] + ns * u[1]);
-                    st4<bf16>(UT + (size_t)j * LDU + MP + 16 * mt + 4 * g, cs * u[1] - ns * u[0]);
-                    st4<bf16>(YT + (size_t)j * LDU + 16 * mt + 4 * g, cs * y[0] + ns * y[1]);
-                    st4<bf16>(YT + (size_t)j * LDU + MP + 16 * mt + 4 * g, cs * y[1] - ns * y[0]);
                 }
+                // E o X with the stored row [c | -s] of token j
+                const floatx4 cs = to_f4(ld4_lds<bf16>(sE + (size_t)j * LE + 16 * mt + 4 * g));
+                const floatx4 ns = to_f4(ld4_lds<bf16>(sE + (size_t)j * LE + MP + 16 * mt + 4 * g));
+                st_lds<bf16x4>(Us + (size_t)j * LDW + P::tcol(j, 16 * mt + 4 * g), cvt4(cs * u[0] + ns * u[1], bf16()));
+                st_lds<bf16x4>(Us + (size_t)j * LDW + P::tcol(j, MP + 16 * mt + 4 * g), cvt4(cs * u[1] - ns * u[0], bf16()));
             }
         }
-        __syncthreads();  // U and Y visible
+        __syncthreads();  // U and Y visible; the Gram tiles no longer read
 
-        // ---- phase 3 (query tile w): scores, softmax and its gradient, the weights, H tiles, dq
+        // ---- phase 3 (query tile w): side 0 the scores and their softmax, side 1 dP; then side 0
+        // the readout weights W'' and H_v, side 1 dz, Wq'' and H_q
         {
             const int j = 16 * w + r;
-            const long long pos = a.t0 + tok0 + j;
-            F uf[KBM], yf[KBM];
+            F uf[KBM];
 #pragma unroll
-            for (int kb = 0; kb < KBM; ++kb) {
-                uf[kb] = ld_frag<bf16>(UT + (size_t)j * LDU, 32 * kb, g);
-                yf[kb] = ld_frag<bf16>(YT + (size_t)j * LDU, 32 * kb, g);
-            }
-            floatx4 sc[NST], dp[NST];
+            for (int kb = 0; kb < KBM; ++kb) uf[kb] = P::ld_row(Us, LDW, j, kb, g);
+            // products with the slot rows: scores (side 0) or scale dP (side 1); folded, the mirror
+            // slots follow the slots
+            floatx4 sc[NST];
+            if constexpr (P::FOLD) {
+                constexpr int KH = KBM / 2;
+                floatx4 sp[NHT], sq[NHT];
 #pragma unroll
-            for (int s4 = 0; s4 < NST; ++s4) {
-                sc[s4] = dp[s4] = zero4();
+                for (int s4 = 0; s4 < NHT; ++s4) {
+                    const bf16* row = sAB + (size_t)(16 * s4 + r) * LE;
+                    sp[s4] = sq[s4] = zero4();
 #pragma unroll
-                for (int kb = 0; kb < KBM; ++kb) {
-                    const F af = ld_frag<bf16>(sAB + (size_t)(16 * s4 + r) * LE, 32 * kb, g);
-                    sc[s4] = mma(af, uf[kb], sc[s4]);
-                    dp[s4] = mma(af, yf[kb], dp[s4]);
-                }
-            }
-            __syncthreads();  // every wave holds its U, Y rows: their buffer takes the weights
-            float mx = -INFINITY;
-#pragma unroll
-            for (int s4 = 0; s4 < NST; ++s4) {
-                const intx4 th = *reinterpret_cast<const intx4*>(sTheta + 16 * s4 + 4 * g);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if (pos < (long long)th[e]) sc[s4][e] = -INFINITY;
-                    mx = fmaxf(mx, sc[s4][e]);
-                }
-            }
-            mx = rows_max(mx);
-            float sum = 0.f;
-#pragma unroll
-            for (int s4 = 0; s4 < NST; ++s4)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float ex = __expf(sc[s4][e] - mx);
-                    sc[s4][e] = ex;
-                    sum += ex;
-                }
-            sum = rows_sum(sum);
-            const float inv = __builtin_amdgcn_rcpf(sum);  // sum >= 1: the maximum slot contributes exp(0)
-            float pd = 0.f;
-#pragma unroll
-            for (int s4 = 0; s4 < NST; ++s4) {
-                sc[s4] = sc[s4] * inv;
-                dp[s4] = dp[s4] * iscale;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) pd += sc[s4][e] * dp[s4][e];
-            }
-            pd = rows_sum(pd);
-            F pf[KBS], zf[KBS];
-#pragma unroll
-            for (int kb = 0; kb < KBS; ++kb) {
-                pf[kb] = frag_from_acc<bf16>(sc[2 * kb] * iscale, sc[2 * kb + 1] * iscale);
-                zf[kb] = frag_from_acc<bf16>(sc[2 * kb] * (dp[2 * kb] - pd), sc[2 * kb + 1] * (dp[2 * kb + 1] - pd));
-            }
-            // [Re W'' | -Im W''] with W'' = (P A - i P B) o rho^j (the slot matrix holds scale (A | B):
-            // pf carries 1 / scale), and H_v
-            {
-                floatx4 wa[2 * NMT];
-#pragma unroll
-                for (int t = 0; t < 2 * NMT; ++t) {
-                    wa[t] = zero4();
-#pragma unroll
-                    for (int kb = 0; kb < KBS; ++kb) wa[t] = mma(ld_frag_tr(sAB, LE, 16 * t, kb, g, r), pf[kb], wa[t]);
-                }
-#pragma unroll
-                for (int mt = 0; mt < NMT; ++mt) {
-                    const floatx4 cs = to_f4(ld4_lds<bf16>(sE + (size_t)j * LE + 16 * mt + 4 * g));
-                    const floatx4 ns = to_f4(ld4_lds<bf16>(sE + (size_t)j * LE + MP + 16 * mt + 4 * g));
-                    const floatx4 am = wa[mt], bm = wa[NMT + mt];
-                    wa[mt] = am * cs - bm * ns;
-                    wa[NMT + mt] = am * ns + bm * cs;
-                    st_lds<bf16x4>(WvT + (size_t)j * P::LDW + P::tcol(j, 16 * mt + 4 * g), cvt4(wa[mt], bf16()));
-                    st_lds<bf16x4>(WvT + (size_t)j * P::LDW + P::tcol(j, MP + 16 * mt + 4 * g), cvt4(wa[NMT + mt], bf16()));
-                }
-                if constexpr (!SUM) {
-                    F wf[KBM];
-#pragma unroll
-                    for (int kb = 0; kb < KBM; ++kb) wf[kb] = frag_from_acc<bf16>(wa[2 * kb], wa[2 * kb + 1]);
-#pragma unroll
-                    for (int kt = 0; kt < NT; ++kt) {
-                        floatx4 hv = zero4();
-                        if (kt <= w) {
-#pragma unroll
-                            for (int kb = 0; kb < KBM; ++kb)
-                                hv = mma(ld_frag<bf16>(sE + (size_t)(16 * kt + r) * LE, 32 * kb, g), wf[kb], hv);
-                            if (kt == w) {
-#pragma unroll
-                                for (int e = 0; e < 4; ++e)
-                                    if (4 * g + e > r) hv[e] = 0.f;
-                            }
-                        }
-                        st_lds<bf16x4>(HvT + (size_t)j * P::LDH + P::tcol(j, 16 * kt + 4 * g), cvt4(hv, bf16()));
+                    for (int kb = 0; kb < KH; ++kb) {
+                        sp[s4] = mma(ld_frag<bf16>(row, 32 * kb, g), uf[kb], sp[s4]);
+                        sq[s4] = mma(ld_frag<bf16>(row + MP, 32 * kb, g), uf[KH + kb], sq[s4]);
                     }
                 }
+                if (last_row) {
+#pragma unroll
+                    for (int kb = 0; kb < KH; ++kb) {
+                        const F f = ld_frag<bf16>(sAB + (size_t)P::HP * LE, 32 * kb, g);
+                        sq[0] = mma(r == 0 ? f : zero_frag<bf16>(), uf[kb], sq[0]);
+                    }
+                }
+                fold_scores<NHT>(sp, sq, g);
+#pragma unroll
+                for (int s4 = 0; s4 < NHT; ++s4) {
+                    sc[s4] = sp[s4];
+                    sc[NHT + s4] = sq[s4];
+                }
+            } else {
+#pragma unroll
+                for (int s4 = 0; s4 < NST; ++s4) {
+                    sc[s4] = zero4();
+#pragma unroll
+                    for (int kb = 0; kb < KBM; ++kb)
+                        sc[s4] = mma(ld_frag<bf16>(sAB + (size_t)(16 * s4 + r) * LE, 32 * kb, g), uf[kb], sc[s4]);
+                }
             }
-            // [Re Wq'' | -Im Wq''] with Wq'' = scale (dz A - i dz B) o rho^j, H_q and dq
-            {
-                floatx4 wq[2 * NMT];
+            // where the slot weights of tile s4 pass from side 0 to side 1 (float32, lane order): the
+            // Gram region, then this query tile's own U rows
+            auto xch = [&](int s4) {
+                float* base = s4 < 4 ? reinterpret_cast<float*>(GT) + (size_t)(w * (NST < 4 ? NST : 4) + s4) * 256
+                                     : reinterpret_cast<float*>(UT + (size_t)16 * w * LDW) + (size_t)(s4 - 4) * 256;
+                return base + 4 * (tid & 63);
+            };
+            if (side == 0) {
+                const long long pos = a.t0 + tok0 + j;
+                float mx = -INFINITY;
 #pragma unroll
-                for (int t = 0; t < 2 * NMT; ++t) {
-                    wq[t] = zero4();
+                for (int s4 = 0; s4 < NST; ++s4) {
+                    const intx4 th = *reinterpret_cast<const intx4*>(sTheta + 16 * s4 + 4 * g);
 #pragma unroll
-                    for (int kb = 0; kb < KBS; ++kb) wq[t] = mma(ld_frag_tr(sAB, LE, 16 * t, kb, g, r), zf[kb], wq[t]);
+                    for (int e = 0; e < 4; ++e) {
+                        if (pos < (long long)th[e]) sc[s4][e] = -INFINITY;
+                        mx = fmaxf(mx, sc[s4][e]);
+                    }
+                }
+                mx = rows_max(mx);
+                float sum = 0.f;
+#pragma unroll
+                for (int s4 = 0; s4 < NST; ++s4)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float ex = __expf(sc[s4][e] - mx);
+                        sc[s4][e] = ex;
+                        sum += ex;
+                    }
+                sum = rows_sum(sum);
+                const float inv = __builtin_amdgcn_rcpf(sum);  // sum >= 1: the maximum slot contributes exp(0)
+#pragma unroll
+                for (int s4 = 0; s4 < NST; ++s4) {
+                    sc[s4] = sc[s4] * inv;
+                    st_lds<floatx4>(xch(s4), sc[s4]);
+                }
+            }
+            __syncthreads();  // slot weights visible; U and Y no longer read
+            // side 0: P / scale (the slot matrix holds scale (A | B)); side 1: dz = P (dP - sum P dP)
+            if (side == 0) {
+#pragma unroll
+                for (int s4 = 0; s4 < NST; ++s4) sc[s4] = sc[s4] * iscale;
+            } else {
+                floatx4 pw[NST];
+                float pd = 0.f;
+#pragma unroll
+                for (int s4 = 0; s4 < NST; ++s4) {
+                    pw[s4] = *(const __attribute__((address_space(3))) floatx4*)xch(s4);
+                    sc[s4] = sc[s4] * iscale;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) pd += pw[s4][e] * sc[s4][e];
+                }
+                pd = rows_sum(pd);
+#pragma unroll
+                for (int s4 = 0; s4 < NST; ++s4) sc[s4] = pw[s4] * (sc[s4] - pd);
+            }
+            // [Re | -Im] of W'' = (P A - i P B) o rho^j, side 1 of Wq'' = scale (dz A - i dz B) o rho^j
+            floatx4 wa[2 * NMT];
+#pragma unroll
+            for (int t = 0; t < 2 * NMT; ++t) wa[t] = zero4();
+            if constexpr (P::FOLD) {
+                floatx4 ep[NHT], eq[NHT];
+#pragma unroll
+                for (int s4 = 0; s4 < NHT; ++s4) {
+                    ep[s4] = sc[s4];
+                    eq[s4] = sc[NHT + s4];
+                }
+                fold_weights<NHT>(ep, eq, g);
+                F pf[P::KBH], qf[P::KBH];
+#pragma unroll
+                for (int kb = 0; kb < P::KBH; ++kb) {
+                    pf[kb] = frag_from_acc<bf16>(ep[2 * kb], ep[2 * kb + 1]);
+                    qf[kb] = frag_from_acc<bf16>(eq[2 * kb], eq[2 * kb + 1]);
                 }
 #pragma unroll
-                for (int mt = 0; mt < NMT; ++mt) {
-                    const floatx4 cs = to_f4(ld4_lds<bf16>(sE + (size_t)j * LE + 16 * mt + 4 * g));
-                    const floatx4 ns = to_f4(ld4_lds<bf16>(sE + (size_t)j * LE + MP + 16 * mt + 4 * g));
-                    const floatx4 am = wq[mt], bm = wq[NMT + mt];
-                    wq[mt] = am * cs - bm * ns;
-                    wq[NMT + mt] = am * ns + bm * cs;
-                    st_lds<bf16x4>(WqT + (size_t)j * P::LDW + P::tcol(j, 16 * mt + 4 * g), cvt4(wq[mt], bf16()));
-                    st_lds<bf16x4>(WqT + (size_t)j * P::LDW + P::tcol(j, MP + 16 * mt + 4 * g), cvt4(wq[NMT + mt], bf16()));
+                for (int t = 0; t < 2 * NMT; ++t)
+#pragma unroll
+                    for (int kb = 0; kb < P::KBH; ++kb)
+                        wa[t] = mma(ld_frag_tr(sAB, LE, 16 * t, kb, g, r), t < NMT ? pf[kb] : qf[kb], wa[t]);
+                if (last_row) {
+#pragma unroll
+                    for (int t = 0; t < NMT; ++t) {
+                        F f = zero_frag<bf16>();
+                        const bf16 x = sAB[(size_t)P::HP * LE + 16 * t + r];
+                        f[0] = g == 0 ? x : (bf16)0.f;
+                        wa[t] = mma(f, qf[0], wa[t]);
+                    }
                 }
-                if constexpr (!SUM) {
-                    F qf2[KBM];
+            } else {
+                F pf[P::KBS];
 #pragma unroll
-                    for (int kb = 0; kb < KBM; ++kb) qf2[kb] = frag_from_acc<bf16>(wq[2 * kb], wq[2 * kb + 1]);
-                    floatx4 oa[NDT];
+                for (int kb = 0; kb < P::KBS; ++kb) pf[kb] = frag_from_acc<bf16>(sc[2 * kb], sc[2 * kb + 1]);
 #pragma unroll
-                    for (int dt = 0; dt < NDT; ++dt) {
-                        oa[dt] = zero4();
+                for (int t = 0; t < 2 * NMT; ++t)
+#pragma unroll
+                    for (int kb = 0; kb < P::KBS; ++kb) wa[t] = mma(ld_frag_tr(sAB, LE, 16 * t, kb, g, r), pf[kb], wa[t]);
+            }
+            bf16* Ws = side ? WqT : WvT;
+#pragma unroll
+            for (int m4 = 0; m4 < NMT; ++m4) {
+                const floatx4 cs = to_f4(ld4_lds<bf16>(sE + (size_t)j * LE + 16 * m4 + 4 * g));
+                const floatx4 ns = to_f4(ld4_lds<bf16>(sE + (size_t)j * LE + MP + 16 * m4 + 4 * g));
+                const floatx4 am = wa[m4], bm = wa[NMT + m4];
+                wa[m4] = am * cs - bm * ns;
+                wa[NMT + m4] = am * ns + bm * cs;
+                st_lds<bf16x4>(Ws + (size_t)j * LDW + P::tcol(j, 16 * m4 + 4 * g), cvt4(wa[m4], bf16()));
+                st_lds<bf16x4>(Ws + (size_t)j * LDW + P::tcol(j, MP + 16 * m4 + 4 * g), cvt4(wa[NMT + m4], bf16()));
+            }
+            if constexpr (!SUM) {
+                F wf[KBM];
+#pragma unroll
+                for (int kb = 0; kb < KBM; ++kb) wf[kb] = frag_from_acc<bf16>(wa[2 * kb], wa[2 * kb + 1]);
+                __syncthreads();  // the slot weights in the Gram region are read: it takes the H tiles
+                bf16* Hs = side ? HqT : HvT;
+#pragma unroll
+                for (int kt = 0; kt < NT; ++kt) {
+                    floatx4 hh = zero4();
+                    if (kt <= w) {
 #pragma unroll
                         for (int kb = 0; kb < KBM; ++kb)
-                            oa[dt] = mma(P::ld_t(ZkT, P::LDZ, 16 * dt, kb, g, r), qf2[kb], oa[dt]);
-                    }
-                    floatx4 hq[NT];
+                            hh = mma(ld_frag<bf16>(sE + (size_t)(16 * kt + r) * LE, 32 * kb, g), wf[kb], hh);
+                        if (kt == w) {
 #pragma unroll
-                    for (int kt = 0; kt < NT; ++kt) {
-                        hq[kt] = zero4();
-                        if (kt <= w) {
-#pragma unroll
-                            for (int kb = 0; kb < KBM; ++kb)
-                                hq[kt] = mma(ld_frag<bf16>(sE + (size_t)(16 * kt + r) * LE, 32 * kb, g), qf2[kb], hq[kt]);
-                            if (kt == w) {
-#pragma unroll
-                                for (int e = 0; e < 4; ++e)
-                                    if (4 * g + e > r) hq[kt][e] = 0.f;
-                            }
-                        }
-                        st_lds<bf16x4>(HqT + (size_t)j * P::LDH + P::tcol(j, 16 * kt + 4 * g), cvt4(hq[kt], bf16()));
-                    }
-#pragma unroll
-                    for (int kb = 0; kb < KBC; ++kb) {
-                        if (2 * kb <= w) {
-                            const F hf = frag_from_acc<bf16>(hq[2 * kb], hq[2 * kb + 1]);
-#pragma unroll
-                            for (int dt = 0; dt < NDT; ++dt)
-                                oa[dt] = mma(ld_frag_tr(Ks, LDQ, 16 * dt, kb, g, r), hf, oa[dt]);
+                            for (int e = 0; e < 4; ++e)
+                                if (4 * g + e > r) hh[e] = 0.f;
                         }
                     }
-                    if (j < c) {
-                        bf16* dqb = (bf16*)a.dq + ((size_t)bh * a.L + tok0 + j) * D;
-#pragma unroll
-                        for (int dt = 0; dt < NDT; ++dt) st4<bf16>(dqb + 16 * dt + 4 * g, oa[dt]);
-                    }
+                    st_lds<bf16x4>(Hs + (size_t)j * P::LDH + P::tcol(j, 16 * kt + 4 * g), cvt4(hh, bf16()));
                 }
             }
         }
         __syncthreads();  // H tiles and weights visible
 
-        // ---- phase 4 (head-dim tiles): Gam'' = conj(rho^c) o Gam'; dk, dv of the wave's d-tile for
-        // every key; Gam' <- Gam'' + [conj(Wq'')^T Q | conj(W'')^T dO]
+        // ---- phase 4 (head-dim tile dt): Gam'' = conj(rho^c) o Gam'; dk (side 1: dv) of every key;
+        // Gam' <- Gam'' + conj(Wq'')^T Q (side 1: conj(W'')^T dO); then a share of dq
+        const bf16* Ws = side ? WvT : WqT;
 #pragma unroll
-        for (int od = 0; od < ODT; ++od) {
-            const int dt = w + NW * od;
-            if (dt >= NDT) continue;
+        for (int m4 = 0; m4 < NMT; ++m4) {
+            const floatx4 cc = ld4f(rc + 16 * m4 + 4 * g), ss = ld4f(rc + MP + 16 * m4 + 4 * g);
+            const floatx4 re = Gm[0][m4], im = Gm[1][m4];
+            Gm[0][m4] = cc * re + ss * im;
+            Gm[1][m4] = cc * im - ss * re;
+        }
+        F xtf[KBC];
 #pragma unroll
-            for (int mt = 0; mt < NMT; ++mt) {
-                const floatx4 cc = ld4f(rc + 16 * mt + 4 * g), ss = ld4f(rc + MP + 16 * mt + 4 * g);
-                floatx4 re = Gk[od][0][mt], im = Gk[od][1][mt];
-                Gk[od][0][mt] = cc * re + ss * im;
-                Gk[od][1][mt] = cc * im - ss * re;
-                re = Gv[od][0][mt];
-                im = Gv[od][1][mt];
-                Gv[od][0][mt] = cc * re + ss * im;
-                Gv[od][1][mt] = cc * im - ss * re;
-            }
-            if constexpr (!SUM) {
-                // A operands [Re Gam'' | Im Gam''] (rows d, reduction over the 2MP rows)
-                F gkf[KBM], gvf[KBM];
+        for (int kb = 0; kb < KBC; ++kb) xtf[kb] = ld_frag_tr(Rs, LDQ, 16 * dt, kb, g, r);
+        if constexpr (!SUM) {
+            const bf16* Hs = side ? HvT : HqT;
+            bf16* out = (bf16*)(side ? a.dv : a.dk) + ((size_t)bh * a.L + tok0) * D;
+            // A operand [Re Gam'' | Im Gam''] (rows d, reduction over the 2MP rows)
+            F gf[KBM];
 #pragma unroll
-                for (int kb = 0; kb < KBM; ++kb) {
-                    // the block's two 16-row tiles in the order [Re tiles | Im tiles]
-                    const int t0 = 2 * kb, t1 = 2 * kb + 1;
-                    gkf[kb] = frag_from_acc<bf16>(Gk[od][t0 / NMT][t0 % NMT], Gk[od][t1 / NMT][t1 % NMT]);
-                    gvf[kb] = frag_from_acc<bf16>(Gv[od][t0 / NMT][t0 % NMT], Gv[od][t1 / NMT][t1 % NMT]);
-                }
-                F qtf[KBC], otf[KBC];
-#pragma unroll
-                for (int kb = 0; kb < KBC; ++kb) {
-                    qtf[kb] = ld_frag_tr(Qs, LDQ, 16 * dt, kb, g, r);
-                    otf[kb] = ld_frag_tr(dOs, LDQ, 16 * dt, kb, g, r);
-                }
-#pragma unroll
-                for (int kt = 0; kt < NT; ++kt) {
-                    const int j = 16 * kt + r;
-                    floatx4 ka = zero4(), va = zero4();
-#pragma unroll
-                    for (int kb = 0; kb < KBC; ++kb) {
-                        ka = mma(qtf[kb], P::ld_t(HqT, P::LDH, 16 * kt, kb, g, r), ka);
-                        va = mma(otf[kb], P::ld_t(HvT, P::LDH, 16 * kt, kb, g, r), va);
-                    }
-#pragma unroll
-                    for (int kb = 0; kb < KBM; ++kb) {
-                        const F ef = ld_frag<bf16>(sE + (size_t)j * LE, 32 * kb, g);
-                        ka = mma(gkf[kb], ef, ka);
-                        va = mma(gvf[kb], ef, va);
-                    }
-                    if (j < c) {
-                        bf16* dkb = (bf16*)a.dk + ((size_t)bh * a.L + tok0 + j) * D;
-                        bf16* dvb = (bf16*)a.dv + ((size_t)bh * a.L + tok0 + j) * D;
-                        st4<bf16>(dkb + 16 * dt + 4 * g, ka);
-                        st4<bf16>(dvb + 16 * dt + 4 * g, va);
-                    }
-                }
+            for (int kb = 0; kb < KBM; ++kb) {
+                // the block's two 16-row tiles in the order [Re tiles | Im tiles]
+                const int t0 = 2 * kb, t1 = 2 * kb + 1;
+                gf[kb] = frag_from_acc<bf16>(Gm[t0 / NMT][t0 % NMT], Gm[t1 / NMT][t1 % NMT]);
             }
 #pragma unroll
-            for (int kb = 0; kb < KBC; ++kb) {
-                const F qtf = ld_frag_tr(Qs, LDQ, 16 * dt, kb, g, r);
-                const F otf = ld_frag_tr(dOs, LDQ, 16 * dt, kb, g, r);
+            for (int kt = 0; kt < NT; ++kt) {
+                if (!mine(kt, rd, P::NRD)) continue;
+                const int j = 16 * kt + r;
+                floatx4 xa = zero4();
 #pragma unroll
-                for (int p = 0; p < 2; ++p)
+                for (int kb = 0; kb < KBC; ++kb)
+                    if (2 * kb + 1 >= kt) xa = mma(xtf[kb], P::ld_t(Hs, P::LDH, 16 * kt, kb, g, r), xa);
 #pragma unroll
-                    for (int mt = 0; mt < NMT; ++mt) {
-                        Gk[od][p][mt] = mma(P::ld_t(WqT, P::LDW, p * MP + 16 * mt, kb, g, r), qtf, Gk[od][p][mt]);
-                        Gv[od][p][mt] = mma(P::ld_t(WvT, P::LDW, p * MP + 16 * mt, kb, g, r), otf, Gv[od][p][mt]);
-                    }
+                for (int kb = 0; kb < KBM; ++kb) xa = mma(gf[kb], ld_frag<bf16>(sE + (size_t)j * LE, 32 * kb, g), xa);
+                if (j < c) st4<bf16>(out + (unsigned)(j * D + 16 * dt + 4 * g), xa);
+            }
+        }
+#pragma unroll
+        for (int kb = 0; kb < KBC; ++kb)
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int m4 = 0; m4 < NMT; ++m4)
+                    Gm[p][m4] = mma(P::ld_t(Ws, LDW, p * MP + 16 * m4, kb, g, r), xtf[kb], Gm[p][m4]);
+        if constexpr (!SUM) {
+            // dq of head-dim tile dt: Re(Wq'' Z'_k) + H_q K, the query tiles split over the sides
+            // (and over the waves that share the tile)
+            F zf[KBM], ktf[KBC];
+#pragma unroll
+            for (int kb = 0; kb < KBM; ++kb) zf[kb] = P::ld_t(ZkT, P::LDZ, 16 * dt, kb, g, r);
+#pragma unroll
+            for (int kb = 0; kb < KBC; ++kb) ktf[kb] = ld_frag_tr(Ks, LDQ, 16 * dt, kb, g, r);
+            bf16* dqb = (bf16*)a.dq + ((size_t)bh * a.L + tok0) * D;
+#pragma unroll
+            for (int tt = 0; tt < NT; ++tt) {
+                if (!mine(tt, P::NRD == 1 ? side : 2 * side + rd, 2 * P::NRD)) continue;
+                const int j = 16 * tt + r;
+                floatx4 oa = zero4();
+#pragma unroll
+                for (int kb = 0; kb < KBM; ++kb) oa = mma(zf[kb], P::ld_row(WqT, LDW, j, kb, g), oa);
+#pragma unroll
+                for (int kb = 0; kb < KBC; ++kb)
+                    if (2 * kb <= tt) oa = mma(ktf[kb], P::ld_row(HqT, P::LDH, j, kb, g), oa);
+                if (j < c) st4<bf16>(dqb + (unsigned)(j * D + 16 * dt + 4 * g), oa);
             }
         }
     }
 
     // ---- the adjoint at the segment's start
+    if (rd != 0) return;
+    if constexpr (SUM) {
+        float* S = a.asum + ((size_t)bh * a.nbk + seg) * 4 * MP * D + (size_t)2 * side * MP * D;
 #pragma unroll
-    for (int od = 0; od < ODT; ++od) {
-        const int dt = w + NW * od;
-        if (dt >= NDT) continue;
-        if constexpr (SUM) {
-            float* S = a.asum + ((size_t)bh * a.nbk + seg) * 4 * MP * D;
+        for (int p = 0; p < 2; ++p)
 #pragma unroll
-            for (int p2 = 0; p2 < 2; ++p2)
+            for (int m4 = 0; m4 < NMT; ++m4)
 #pragma unroll
-                for (int p = 0; p < 2; ++p)
+                for (int e = 0; e < 4; ++e) S[((size_t)p * MP + 16 * m4 + 4 * g + e) * D + 16 * dt + r] = Gm[p][m4][e];
+    } else {
+        float* gin = side ? a.gv_in : a.gk_in;
+        if (seg != 0 || !gin) return;
 #pragma unroll
-                    for (int mt = 0; mt < NMT; ++mt) {
-                        const floatx4 x = p2 ? Gv[od][p][mt] : Gk[od][p][mt];
+        for (int m4 = 0; m4 < NMT; ++m4)
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            S[((size_t)(2 * p2 + p) * MP + 16 * mt + 4 * g + e) * D + 16 * dt + r] = x[e];
-                    }
-        } else {
-            if (seg != 0) continue;
-#pragma unroll
-            for (int mt = 0; mt < NMT; ++mt)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int m = 16 * mt + 4 * g + e;
-                    if (m >= a.M) continue;
-                    const float c1 = rho1[m], s1 = rho1[MP + m];
-                    const size_t o0 = (((size_t)bh * 2 + 0) * a.M + m) * D + 16 * dt + r;
-                    const size_t o1 = (((size_t)bh * 2 + 1) * a.M + m) * D + 16 * dt + r;
-                    if (a.gk_in) {
-                        const float re = Gk[od][0][mt][e], im = Gk[od][1][mt][e];
-                        a.gk_in[o0] = c1 * re + s1 * im;
-                        a.gk_in[o1] = c1 * im - s1 * re;
-                    }
-                    if (a.gv_in) {
-                        const float re = Gv[od][0][mt][e], im = Gv[od][1][mt][e];
-                        a.gv_in[o0] = c1 * re + s1 * im;
-                        a.gv_in[o1] = c1 * im - s1 * re;
-                    }
-                }
-        }
+            for (int e = 0; e < 4; ++e) {
+                const int m = 16 * m4 + 4 * g + e;
+                if (m >= a.M) continue;
+                const float c1 = rho1[m], s1 = rho1[MP + m], re = Gm[0][m4][e], im = Gm[1][m4][e];
+                gin[(((size_t)bh * 2 + 0) * a.M + m) * D + 16 * dt + r] = c1 * re + s1 * im;
+                gin[(((size_t)bh * 2 + 1) * a.M + m) * D + 16 * dt + r] = c1 * im - s1 * re;
+            }
     }
 }
 
@@ -866,11 +824,11 @@ hipError_t launch_backward16_shape(const BwdArgs& a, hipStream_t s, void* const*
     if (e != hipSuccess || (e = mark(0)) != hipSuccess) return e;
     if (a.nseg > 1) {
         const unsigned sum_blocks = (unsigned)(a.nbk - a.nbk / a.nseg);  // blocks of segments 1..nseg-1
-        hipLaunchKernelGGL((bwd16_kernel<D, MP, SP, true>), dim3(units * sum_blocks), dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL((bwd16_kernel<D, MP, SP, true>), dim3(units * sum_blocks), dim3(Bwd16<D, MP, SP>::NTHR), 0, s, a);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if ((e = mark(1)) != hipSuccess) return e;
-    hipLaunchKernelGGL((bwd16_kernel<D, MP, SP, false>), dim3(units * a.nseg), dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((bwd16_kernel<D, MP, SP, false>), dim3(units * a.nseg), dim3(Bwd16<D, MP, SP>::NTHR), 0, s, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     return mark(2);
 }

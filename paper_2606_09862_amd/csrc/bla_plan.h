@@ -236,7 +236,7 @@ struct BwdArgs {
     const double* rperiod; // [H] 1 / T
     float* fsum;           // [B*H][nbk][2][2][MP][D] forward summaries of the blocks
     float* asum;           // [B*H][nbk][2][2][MP][D] adjoint summaries (blocks of segment 0 unused)
-    int B, H, L, M;
+    int B, H, L, M, S;
     int nch, nseg, cps;    // chunks per sequence, segments, chunks per segment
     int nbk, cpb;          // summary blocks per sequence (nseg times a power of two), chunks per block
     long long t0;

@@ -94,3 +94,21 @@ def test_forward(dtype, d, M, S, anchor):
         assert_close(o.float().cpu().numpy(), ref, TOL[dtype], f"O part {part}")
         # far along the sequence: every threshold passed
         sk, sv, t0 = nk, nv, 4 * (2 * M - 1)
+
+
+BWD_CASES = [  # d, M, S: the slot edges, and every way the waves of a side share mode and head-dim tiles
+    (64, 64, 64), (64, 64, 63), (64, 64, 65), (64, 64, 127), (64, 64, 128), (64, 33, 34), (64, 32, 64), (64, 32, 63),
+    (64, 32, 32), (64, 16, 31), (64, 5, 9), (32, 64, 128), (32, 64, 20), (32, 32, 64), (32, 17, 33), (32, 16, 16),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,M,S", BWD_CASES)
+def test_backward(d, M, S):
+    """A ragged last chunk, input states and gradients of the final states, from a masked start."""
+    import bla_inputs as bi
+    from test_gpu_backward import run_bwd, tensors
+    (q, k, v, g), (sk, sv, gk, gv) = tensors(S + M, 2, 3, 64 * 5 - 17, d, M, torch.bfloat16, with_states=True)
+    q = bi.round_bf16(q * 4.0)
+    T = [2.0 * M - 1.0, 2.3 * (2 * M - 1), 4.0 * M]
+    run_bwd(q, k, v, g, T, M, S, torch.bfloat16, t0=3, sk=sk, sv=sv, gk=gk, gv=gv, label=f"folding d={d} M={M} S={S}")
