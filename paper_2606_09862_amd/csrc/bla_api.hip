@@ -311,6 +311,22 @@ bla_status build_tables(const Plan& pl, const double* T, char* ws, hipStream_t s
     return BLA_OK;
 }
 
+// The heads' clamped periods for the decay kernels, with the table kernel only where there are
+// more of them than travel with a launch.
+bla_status decay_periods(const Plan& pl, const double* T, char* ws, hipStream_t s, int reuse, DecayPeriods* out)
+{
+    memset(out, 0, sizeof(*out));
+    if (pl.H > kMaxHeadsPerTableLaunch) {
+        out->tab = (const double*)(ws + pl.off_period);
+        return build_tables(pl, T, ws, s, true, reuse);
+    }
+    for (int h = 0; h < pl.H; ++h) {
+        const double tmin = 2.0 * pl.M - 1.0;
+        out->val[h] = T[h] < tmin ? tmin : T[h];
+    }
+    return BLA_OK;
+}
+
 // Decay form: the tables of a decode-step plan plus the segment summaries.  Sequences are
 // cut into segments (a multiple of 16 tokens, at least 32) until the forward launch has
 // about two waves per SIMD, within a 512 MB cap on the summaries.
@@ -687,7 +703,8 @@ static bla_status decay_forward_impl(const bla_params* p, const double* T, const
         return !events || !events[i] || hipEventRecord((hipEvent_t)events[i], s) == hipSuccess;
     };
     if (!mark(0)) return BLA_ERR_HIP;
-    if ((st = build_tables(pl, T, ws, s, true, p->reuse_tables)) != BLA_OK) return st;
+    DecayPeriods periods;
+    if ((st = decay_periods(pl, T, ws, s, p->reuse_tables, &periods)) != BLA_OK) return st;
     DecayArgs a;
     memset(&a, 0, sizeof(a));
     a.q = q;
@@ -698,9 +715,7 @@ static bla_status decay_forward_impl(const bla_params* p, const double* T, const
     a.sv_in = slot_v_in;
     a.sk_out = slot_k_out;
     a.sv_out = slot_v_out;
-    a.theta = (const int*)(ws + pl.off_theta);
-    a.period = (const double*)(ws + pl.off_period);
-    a.rperiod = (const double*)(ws + pl.off_rperiod);
+    a.T = periods;
     a.summ = (float*)(ws + dp.off_summ);
     a.gE = (const float*)(ws + dp.off_gE);
     a.gB = (const float*)(ws + dp.off_gB);
@@ -794,7 +809,8 @@ bla_status bla_decay_step(const bla_params* p, const double* T, const void* q, c
     if (!workspace || workspace_bytes < pl.total || !aligned16(workspace)) return BLA_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)workspace;
-    if ((st = build_tables(pl, T, ws, s, true, p->reuse_tables)) != BLA_OK) return st;
+    DecayPeriods periods;
+    if ((st = decay_periods(pl, T, ws, s, p->reuse_tables, &periods)) != BLA_OK) return st;
     DecayStepArgs a;
     memset(&a, 0, sizeof(a));
     a.q = q;
@@ -804,8 +820,7 @@ bla_status bla_decay_step(const bla_params* p, const double* T, const void* q, c
     a.pos = pos;
     a.sk = slot_k;
     a.sv = slot_v;
-    a.theta = (const int*)(ws + pl.off_theta);
-    a.rperiod = (const double*)(ws + pl.off_rperiod);
+    a.T = periods;
     a.B = p->B;
     a.H = p->H;
     a.M = p->M;

@@ -92,6 +92,12 @@ __device__ __forceinline__ float dirichlet_at(double fx, int s, double rS, int N
     return sinpif((float)a) / ((float)N * sinpif((float)f));
 }
 
+// First position at which slot s is visible (INT32_MAX past S), as the tables kernel rounds it.
+__device__ __forceinline__ int decay_threshold(int s, int S, double T)
+{
+    return s < S ? (int)rint((double)s * T / (double)S) : INT32_MAX;
+}
+
 // Floats of one segment summary: K~ [SP][D], V~ [SP][D], gate product [SP].
 template <int D, int SP> constexpr size_t decay_summary_floats() { return (size_t)2 * SP * D + SP; }
 
@@ -220,7 +226,8 @@ __global__ __launch_bounds__((DecayGeo<D, SP>::NTH)) void decay_forward_kernel(D
     T* KT = BF ? nullptr : sKV + 16 * G::LKF;          // float32: [D][LKT]
     T* VT = BF ? nullptr : KT + D * G::LKT;            // float32: [D][LKT]
 
-    for (int i = tid; i < SP; i += NTH) sTheta[i] = a.theta[(size_t)h * SP + i];
+    const double Tp = a.T.of(h);
+    for (int i = tid; i < SP; i += NTH) sTheta[i] = decay_threshold(i, a.S, Tp);
 
     // ---- state: Kt[t][dt] = K~^T tile (d rows 16dt.., slot columns), Vt[t][dt] = V~ tile
     // (slot rows, d columns 16dt..) of the wave's slot tile t
@@ -632,7 +639,7 @@ __global__ __launch_bounds__((decay_step_threads<D, SP>())) void decay_step_kern
     const int tid = threadIdx.x, rg = tid / NQ, qd = tid % NQ;
     const int S = a.S, N = 2 * a.M - 1;
     const long long pos = a.pos ? (long long)a.pos[b] : a.t0;
-    const double rT = a.rperiod[h], rS = 1.0 / (double)S;
+    const double Tp = a.T.of(h), rT = 1.0 / Tp, rS = 1.0 / (double)S;
     float* skb = a.sk + (size_t)bh * S * D;
     float* svb = a.sv + (size_t)bh * S * D;
 
@@ -675,7 +682,7 @@ __global__ __launch_bounds__((decay_step_threads<D, SP>())) void decay_step_kern
     if (tid < 64) {
         float mx = -INFINITY;
         for (int s = tid; s < SP; s += 64) {
-            const float z = (s < S && pos >= (long long)a.theta[(size_t)h * SP + s]) ? sz[s] * a.scale : -INFINITY;
+            const float z = (s < S && pos >= (long long)decay_threshold(s, S, Tp)) ? sz[s] * a.scale : -INFINITY;
             sz[s] = z;
             mx = fmaxf(mx, z);
         }

@@ -156,6 +156,16 @@ struct StepArgs {
 };
 
 // State-decay form (Sec. 3.4): slot states [B][H][S][d] float32.
+// Clamped periods of the heads: the decay kernels need nothing else that a head's tables hold (the
+// start-mask threshold of slot s is rint(s T / S)), so up to kMaxHeadsPerTableLaunch of them travel
+// with the launch and no table kernel runs (4 us of a decode step's 25 us at 64 sequences of 16
+// heads, 127 slots); more heads read the table kernel's array.
+struct DecayPeriods {
+    double val[kMaxHeadsPerTableLaunch];
+    const double* tab;  // [H], or null
+    __host__ __device__ double of(int h) const { return tab ? tab[h] : val[h]; }
+};
+
 struct DecayArgs {
     const void* q;
     const void* k;
@@ -165,9 +175,7 @@ struct DecayArgs {
     const float* sv_in;
     float* sk_out;
     float* sv_out;
-    const int* theta;       // [H][SP] start-mask thresholds (INT32_MAX for padded slots)
-    const double* period;   // [H] clamped period T
-    const double* rperiod;  // [H] 1 / T
+    DecayPeriods T;
     float* summ;            // [B*H][nseg-1] segment summaries, scanned in place into entering states
     // Sub-block schedule of the call, per distinct period u (heads map to it through gmap):
     // sub-blocks never cross a 16-token window of the sequence; glen[u][t] is the length of
@@ -203,8 +211,7 @@ struct DecayStepArgs {
     const int64_t* pos;
     float* sk;
     float* sv;
-    const int* theta;
-    const double* rperiod;
+    DecayPeriods T;
     int B, H, M, S;
     long long t0;
     float scale;
