@@ -3,12 +3,13 @@
 // replaces the softmax of), the heads run the operator of Sec. 3.1 (bla_forward), and an
 // output projection mixes the heads back into the model width.
 //
-//   qkv = x W_qkv        x [B*L, D], W_qkv [D, 3D]   (hipBLASLt, bf16 in, float32 accumulation)
+//   qkv = x W_qkv        x [B*L, D], W_qkv [D, 3D]   (bf16 in, float32 accumulation)
 //   o = BLA(q, k, v)     q, k, v read in place from qkv, viewed as [B, L, 3, H, d], and o
 //                        written in place as [B, L, H, d] (the operator's strided form)
-//   y = o W_o            W_o [D, D]                   (hipBLASLt)
+//   y = o W_o            W_o [D, D]
 //
-// The two products are plain dense GEMMs, so they go to the vendor library; the operator
+// The two products are plain dense GEMMs: small widths run gemm_kernel, large ones the vendor
+// library (gemm_takes); the operator
 // runs in this library's kernels and reads and writes the GEMMs' row-major tensors
 // directly, so no head split or merge pass touches memory.
 #include <stdint.h>
@@ -50,6 +51,7 @@ hipblasLtHandle_t gemm_handle()
 bool gemm_rowmajor(const bf16* X, const bf16* W, bf16* Y, long long m, long long n, long long k, void* ws,
                    size_t ws_bytes, hipStream_t s)
 {
+    if (gemm_takes(m, n, k)) return launch_gemm(X, W, Y, m, (int)n, (int)k, s) == hipSuccess;
     hipblasLtHandle_t h = gemm_handle();
     if (!h) return false;
     hipblasLtMatmulDesc_t desc = nullptr;

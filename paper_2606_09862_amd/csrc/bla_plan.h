@@ -280,6 +280,9 @@ hipError_t launch_summary(const Plan& p, const FwdArgs& a, hipStream_t s);
 hipError_t launch_scan(const Plan& p, const FwdArgs& a, hipStream_t s);
 hipError_t launch_forward(const Plan& p, const FwdArgs& a, hipStream_t s);
 hipError_t launch_state_copy(const float* src, float* dst, size_t n, hipStream_t s);
+// Row-major Y [m, n] = X [m, k] W [k, n] in bf16 (16-byte aligned), for the sizes gemm_takes().
+bool gemm_takes(long long m, long long n, long long k);
+hipError_t launch_gemm(const __bf16* X, const __bf16* W, __bf16* Y, long long m, int n, int k, hipStream_t s);
 hipError_t launch_step(const Plan& p, const StepArgs& a, hipStream_t s);
 hipError_t launch_decay_forward(int bf16_io, int D, int SP, const DecayArgs& a, hipStream_t s,
                                 void* const* events);
