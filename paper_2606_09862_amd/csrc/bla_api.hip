@@ -157,7 +157,10 @@ void make_plan_for(const bla_params* p, bool step, bool one_per_cu, Plan* pl)
     }
     if (!step && units > 0 && pl->nch > 1) {
         const int cus = device_cu_count();
-        const long long target = (long long)cus * (one_per_cu ? 1 : pl->upw);  // units that fill every CU once
+        // units that fill every CU once (the one-unit kernel: twice, where two workgroups share one;
+        // 128 sequences of 1024 tokens in 32-token chunks, d = 64, M = 32, 63 slots: 90 -> 73 us)
+        const int fill = pl->pair ? pl->upw : forward_wgs_per_cu(pl->bf16, pl->D, pl->MP, pl->SP, pl->C);
+        const long long target = (long long)cus * (one_per_cu ? 1 : fill);
         if (units < target) {
             long long want = (target + units - 1) / units;
             // A scan over the segments takes about 0.125 us each and a chunk of a segment 6.8 us
@@ -227,11 +230,11 @@ void make_plan_for(const bla_params* p, bool step, bool one_per_cu, Plan* pl)
 void make_plan(const bla_params* p, bool step, Plan* pl)
 {
     make_plan_for(p, step, false, pl);
-    // 128 padded slots at 64 modes and d = 64 run two units per workgroup, and take the segment
-    // summaries that go with them, only because the slot matrix is held folded.  Half the
-    // segments (the one unit per workgroup that an unfolded matrix leaves room for) need half
-    // the scratch: where that is what fits bla_forward_noalloc's fixed array, the plan keeps to it.
-    if (pl->pair && pl->upw == 2 && pl->SP == 128 && pl->total > BLA_NOALLOC_SCRATCH_BYTES) {
+    // Two units (128 padded slots at 64 modes and d = 64, whose slot matrix is held folded) or two
+    // one-unit workgroups per compute unit take twice the segments, and scratch, that one would.
+    // Where only one's fits bla_forward_noalloc's fixed array, the plan keeps to it.
+    if (((pl->pair && pl->upw == 2 && pl->SP == 128) || (!pl->pair && !step)) &&
+        pl->total > BLA_NOALLOC_SCRATCH_BYTES) {
         Plan alt;
         make_plan_for(p, step, true, &alt);
         if (alt.total <= BLA_NOALLOC_SCRATCH_BYTES) *pl = alt;

@@ -27,15 +27,15 @@ __global__ __launch_bounds__(kThreads) void tables_kernel(TableArgs a)
 {
     const int MP = a.MP, MP2 = 2 * MP, C = a.C;
     const int J = a.jrows;                                      // rows j = 0..J-1 (stride C + 1)
-    const long long n_head = (long long)a.nh * J * MP;          // (h, j, m)
-    const long long n_misc = (long long)a.nh * (a.SP + MP);     // theta, rotblk
-    const long long n_ab = a.with_shared ? (long long)a.SP * MP : 0;
-    const long long n_trig = a.with_shared ? (long long)a.SP : 0;
-    const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    // 32-bit indices: at most 64 heads of 129 x 128 phases
+    const int n_head = a.nh * J * MP;          // (h, j, m)
+    const int n_misc = a.nh * (a.SP + MP);     // theta, rotblk
+    const int n_ab = a.with_shared ? a.SP * MP : 0;
+    const int n_trig = a.with_shared ? a.SP : 0;
+    const int gid = blockIdx.x * kThreads + threadIdx.x;
     if (gid < n_head) {
-        const int hl = (int)(gid / (J * MP));
-        const int rem = (int)(gid % (J * MP));
-        const int j = rem / MP, m = rem % MP, h = a.h0 + hl;
+        const int lm = __builtin_ctz(MP);      // MP is a power of two
+        const int m = gid & (MP - 1), hj = gid >> lm, hl = hj / J, j = hj - hl * J, h = a.h0 + hl;
         double sn = 0.0, cs = 0.0;
         if (m < a.M) mode_phase((long long)m * j, 1.0 / a.T[hl], &sn, &cs);
         float* E32 = a.E32 + (size_t)h * (C + 1) * MP2;
@@ -62,8 +62,7 @@ __global__ __launch_bounds__(kThreads) void tables_kernel(TableArgs a)
         return;
     }
     if (gid < n_head + n_misc) {
-        const long long e = gid - n_head;
-        const int hl = (int)(e / (a.SP + MP)), k = (int)(e % (a.SP + MP)), h = a.h0 + hl;
+        const int e = gid - n_head, hl = e / (a.SP + MP), k = e - hl * (a.SP + MP), h = a.h0 + hl;
         const double Tp = a.T[hl];
         if (k < a.SP) {
             a.theta[(size_t)h * a.SP + k] = k < a.S ? (int)rint((double)k * Tp / (double)a.S) : INT32_MAX;
@@ -83,8 +82,7 @@ __global__ __launch_bounds__(kThreads) void tables_kernel(TableArgs a)
     if (gid < n_head + n_misc + n_ab) {
         // Interpolation matrices (Eq. translated at tau_s = s T / S): the phase
         // m w tau_s = 2 pi m s / S does not depend on the head's period.
-        const long long e = gid - n_head - n_misc;
-        const int s = (int)(e / MP), m = (int)(e % MP);
+        const int e = gid - n_head - n_misc, s = e >> __builtin_ctz(MP), m = e & (MP - 1);
         float ca = 0.f, sa = 0.f;
         if (s < a.S && m < a.M) {
             const double cm = (m == 0 ? 1.0 : 2.0) / (2.0 * a.M - 1.0);
@@ -103,7 +101,7 @@ __global__ __launch_bounds__(kThreads) void tables_kernel(TableArgs a)
     }
     if (gid < n_head + n_misc + n_ab + n_trig) {
         // cos | sin of 2 pi k / S: the slot matrices are c_m times these at k = m s mod S
-        const int k = (int)(gid - n_head - n_misc - n_ab);
+        const int k = gid - n_head - n_misc - n_ab;
         double sn = 0.0, cs = 0.0;
         if (k < a.S) sincospi(2.0 * (double)k / (double)a.S, &sn, &cs);
         a.trig[k] = (float)cs;

@@ -42,6 +42,19 @@ int forward_units_per_wg(int is_bf16, int D, int MP, int SP)
     return 0;
 }
 
+#define BLA_WGS_CASE(TT, DD, MMP, SSP) \
+    if (D == DD && MP == MMP && SP == SSP) return one_unit_wgs<TT, DD, MMP, SSP>(C);
+
+int forward_wgs_per_cu(int is_bf16, int D, int MP, int SP, int C)
+{
+    if (is_bf16) {
+        BLA_FOR_EACH_SHAPE(BLA_WGS_CASE, bf16)
+    } else {
+        BLA_FOR_EACH_SHAPE(BLA_WGS_CASE, float)
+    }
+    return 1;
+}
+
 bool forward_supported(int is_bf16, int D, int MP, int SP, int C)
 {
     if (is_bf16) {
