@@ -73,6 +73,22 @@ template <typename T, int D, int MP, int CC = kChunk> struct Geo {
     // fragment over chunk tokens then carries zeros in reduction indices 16..31.
     static constexpr bool HALF = C % 32 != 0;
     static constexpr int OWN = (NMT + NW - 1) / NW;  // mode tiles owned per wave
+    // With fewer mode tiles than waves, NRM waves share a mode tile: wave w has tile w % NMT and is
+    // its part w / NMT.  They split its token tiles in phases A and B and its head-dim tiles of
+    // Z'_v in step (10); Z'_k, whose query products reduce over every head dim, each of them keeps
+    // whole.  (In float32, where a 16 x 16 x 32 product takes 256 cycles, the waves without a tile
+    // were the kernel's time: 32 sequences of 1000 tokens, d = 64, M = 32, 63 slots 71 -> 63 us;
+    // M = 16, 31 slots, 1500 tokens 80 -> 63.)
+    static constexpr int NRM = NMT < NW ? NW / NMT : 1;
+    static constexpr bool token_tile_of(int ct, int part)
+    {
+        // causal work grows with the token tile: 0, 3 | 1, 2 for two parts of four tiles
+        return NRM == 1 || (NRM == 2 && NT == 4 ? (ct == 1 || ct == 2) == (part == 1) : ct % NRM == part);
+    }
+    static constexpr bool dim_tile_of(int dt, int part)
+    {
+        return NRM == 1 || (NDT >= NRM ? dt / (NDT >= NRM ? NDT / NRM : 1) : dt) == part;
+    }
     // Row padding in LDS: rows of a fragment read (16 lanes, one row each, 8 bytes per
     // lane for bf16) land on distinct banks when the row stride is 8 bytes past a
     // multiple of 128 (4 elements); for float32 rows the same 4 elements keep the
@@ -301,10 +317,11 @@ __device__ __forceinline__ void write_zvt(T* ZvT, const StateTiles<T, D, MP, CC>
     using GG = Geo<T, D, MP, CC>;
 #pragma unroll
     for (int o = 0; o < GG::OWN; ++o) {
-        const int mt = w + GG::NW * o;
+        const int mt = (GG::NRM > 1 ? w % GG::NMT : w) + GG::NW * o;
         if (mt < GG::NMT) {
 #pragma unroll
             for (int dt = 0; dt < GG::NDT; ++dt) {
+                if (GG::NRM > 1 && !GG::dim_tile_of(dt, w / GG::NMT)) continue;
                 st4<T>(ZvT + (size_t)(16 * dt + r) * GG::LDZ + 16 * mt + 4 * g, Zv[o][0][dt]);
                 st4<T>(ZvT + (size_t)(16 * dt + r) * GG::LDZ + MP + 16 * mt + 4 * g, -Zv[o][1][dt]);
             }
@@ -364,7 +381,9 @@ __device__ __forceinline__ void advance_owned(StateTiles<T, D, MP, CC>& Zk, Stat
 // rhoC: the row rho^C (full chunks); rhoL: the row rho^c of the sequence's last chunk;
 // E32 (row stride 2MP): phase table for the ragged chunk's rho^{c-i} fragments;
 // Erev / ldR: the [2MP][C] table of rho^{C-i} (full chunks).
-template <typename T, int D, int MP, int CC = kChunk>
+// KSPLIT: the waves that share a mode tile also split its head-dim tiles of Z'_k (the summaries,
+// which have no query products).
+template <typename T, int D, int MP, int CC = kChunk, bool KSPLIT = false>
 __device__ __forceinline__ void advance_state(StateTiles<T, D, MP, CC>& Zk, StateTiles<T, D, MP, CC>& Zv,
                                               const T* Kt, const T* Vt, const float* rhoC,
                                               const float* rhoL, const float* E32, const T* Erev, int ldR,
@@ -375,9 +394,10 @@ __device__ __forceinline__ void advance_state(StateTiles<T, D, MP, CC>& Zk, Stat
     // rho^c: a chunk shorter than C is the sequence's last one, whose row is rhoL (held where
     // rhoC is, so that the selected row is read with loads of one address space)
     const float* Ec = (c == GG::C) ? rhoC : rhoL;
+    const int w0 = w % GG::NMT * (GG::NRM > 1) + w * (GG::NRM == 1), part = GG::NRM > 1 ? w / GG::NMT : 0;
 #pragma unroll
     for (int o = 0; o < GG::OWN; ++o) {
-        const int mt = w + GG::NW * o;
+        const int mt = w0 + GG::NW * o;
         if (mt < GG::NMT) {
             const float cc = Ec[16 * mt + r], ss = Ec[MP + 16 * mt + r];
 #pragma unroll
@@ -402,7 +422,7 @@ __device__ __forceinline__ void advance_state(StateTiles<T, D, MP, CC>& Zk, Stat
         F ef[GG::OWN][2];
 #pragma unroll
         for (int o = 0; o < GG::OWN; ++o) {
-            const int mt = min(w + GG::NW * o, GG::NMT - 1);
+            const int mt = min(w0 + GG::NW * o, GG::NMT - 1);
 #pragma unroll
             for (int p = 0; p < 2; ++p)
                 ef[o][p] = (c == GG::C) ? ld_frag_c<T, CC>(Erev + (size_t)(16 * (p * GG::NMT + mt) + r) * ldR, kb, g)
@@ -410,15 +430,17 @@ __device__ __forceinline__ void advance_state(StateTiles<T, D, MP, CC>& Zk, Stat
         }
 #pragma unroll
         for (int dt = 0; dt < GG::NDT; ++dt) {
-            const F kf = ld_frag_c<T, CC>(Kt + (size_t)(16 * dt + r) * GG::LDK, kb, g);
-            const F vf = ld_frag_c<T, CC>(Vt + (size_t)(16 * dt + r) * GG::LDK, kb, g);
+            const bool own_v = GG::dim_tile_of(dt, part), own_k = !KSPLIT || own_v;
+            F kf, vf;
+            if (own_k) kf = ld_frag_c<T, CC>(Kt + (size_t)(16 * dt + r) * GG::LDK, kb, g);
+            if (own_v) vf = ld_frag_c<T, CC>(Vt + (size_t)(16 * dt + r) * GG::LDK, kb, g);
 #pragma unroll
             for (int o = 0; o < GG::OWN; ++o) {
-                if (w + GG::NW * o < GG::NMT) {
+                if (w0 + GG::NW * o < GG::NMT) {
 #pragma unroll
                     for (int p = 0; p < 2; ++p) {
-                        Zk[o][p][dt] = mma(kf, ef[o][p], Zk[o][p][dt]);
-                        Zv[o][p][dt] = mma(ef[o][p], vf, Zv[o][p][dt]);
+                        if (own_k) Zk[o][p][dt] = mma(kf, ef[o][p], Zk[o][p][dt]);
+                        if (own_v) Zv[o][p][dt] = mma(ef[o][p], vf, Zv[o][p][dt]);
                     }
                 }
             }
@@ -473,17 +495,18 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void summary_kernel(FwdA
             stage_load<T, D, MP, false, CC>(st1, nullptr, kbase + tok * ts, vbase + tok * ts, ts, GG::C, tid);
         }
         __syncthreads();
-        advance_state<T, D, MP, CC>(Zk, Zv, Kt, Vt, rhoC, rhoC, E32h, ErevTh, GG::C, GG::C, w, g, r);
+        advance_state<T, D, MP, CC, true>(Zk, Zv, Kt, Vt, rhoC, rhoC, E32h, ErevTh, GG::C, GG::C, w, g, r);
     }
     float* S = a.summ + ((size_t)bh * a.nbs + blk) * 4 * MP * D;
 #pragma unroll
     for (int o = 0; o < GG::OWN; ++o) {
-        const int mt = w + GG::NW * o;
+        const int mt = (GG::NRM > 1 ? w % GG::NMT : w) + GG::NW * o;
         if (mt < GG::NMT) {
 #pragma unroll
             for (int p = 0; p < 2; ++p)
 #pragma unroll
                 for (int dt = 0; dt < GG::NDT; ++dt) {
+                    if (GG::NRM > 1 && !GG::dim_tile_of(dt, w / GG::NMT)) continue;
                     st4f(S + ((size_t)p * MP + 16 * mt + r) * D + 16 * dt + 4 * g, Zk[o][p][dt]);
                     st4f(S + (size_t)2 * MP * D + ((size_t)p * D + 16 * dt + r) * MP + 16 * mt + 4 * g,
                          Zv[o][p][dt]);
@@ -518,6 +541,7 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdA
     const int tid = threadIdx.x, g = (tid & 63) >> 4, r = tid & 15;
     const int tid_ = tid, g_ = g, r_ = r;  // the chunk loop re-derives its own copies
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, held in a scalar register
+    const int w0 = GG::NRM > 1 ? w % NMT : w, part = GG::NRM > 1 ? w / NMT : 0;  // first owned mode tile, part of it
     const int seg = blockIdx.x % a.nseg, bh = blockIdx.x / a.nseg, h = bh % a.H;
     const int ch0 = seg * a.cps;
     const int nch = min(a.cps, a.nch - ch0);
@@ -628,7 +652,7 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdA
         const float* E1 = rho1;
 #pragma unroll
         for (int o = 0; o < OWN; ++o) {
-            const int mt = w + NW * o;
+            const int mt = w0 + NW * o;
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt) {
                 floatx4 kr = zero4(), ki = zero4(), vr = zero4(), vi = zero4();
@@ -663,7 +687,7 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdA
         const float* cy = a.carry + ((size_t)bh * (a.nseg - 1) + (seg - 1)) * 4 * MP * D;
 #pragma unroll
         for (int o = 0; o < OWN; ++o) {
-            const int mt = w + NW * o;
+            const int mt = w0 + NW * o;
 #pragma unroll
             for (int p = 0; p < 2; ++p)
 #pragma unroll
@@ -768,7 +792,7 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdA
             }
 #pragma unroll
             for (int o = 0; o < OWN; ++o) {
-                if (w + NW * o < NMT) {
+                if (w0 + NW * o < NMT && GG::token_tile_of(ct, part)) {
 #pragma unroll
                     for (int p = 0; p < 2; ++p)
 #pragma unroll
@@ -829,10 +853,11 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdA
         } else
 #pragma unroll
         for (int o = 0; o < OWN; ++o) {
-            const int mt = w + NW * o;
+            const int mt = w0 + NW * o;
             if (mt < NMT) {
 #pragma unroll
                 for (int ct = 0; ct < NT; ++ct) {
+                    if (!GG::token_tile_of(ct, part)) continue;
 #pragma unroll
                     for (int kb = 0; kb < GG::KBC; ++kb) {
                         if (2 * kb <= ct) {
@@ -1284,19 +1309,19 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdA
         const float* E1 = rho1;
 #pragma unroll
         for (int o = 0; o < OWN; ++o) {
-            const int mt = w + NW * o;
+            const int mt = w0 + NW * o;
             if (mt < NMT) {
                 const int m = 16 * mt + r;
                 const float c1 = E1[m], s1 = E1[MP + m];
                 const floatx4 cv = ld4f(E1 + 16 * mt + 4 * g), sv = ld4f(E1 + MP + 16 * mt + 4 * g);
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt) {
-                    if (a.sk_out && m < a.M) {
+                    if (a.sk_out && m < a.M && part == 0) {
                         const floatx4 re = Zk[o][0][dt], im = Zk[o][1][dt];
                         st4f(a.sk_out + (((size_t)bh * 2 + 0) * a.M + m) * D + 16 * dt + 4 * g, c1 * re + s1 * im);
                         st4f(a.sk_out + (((size_t)bh * 2 + 1) * a.M + m) * D + 16 * dt + 4 * g, c1 * im - s1 * re);
                     }
-                    if (a.sv_out) {
+                    if (a.sv_out && GG::dim_tile_of(dt, part)) {
                         const floatx4 re = Zv[o][0][dt], im = Zv[o][1][dt];
                         const floatx4 nr = cv * re + sv * im, ni = cv * im - sv * re;
 #pragma unroll
