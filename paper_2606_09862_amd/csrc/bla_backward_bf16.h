@@ -265,6 +265,64 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
 }
 
 // ---------------------------------------------------------------------------------
+// Scans over the block summaries, in place, for sequences cut into many blocks (kBwdScanBlocks):
+// summary j becomes the pre-rotated state after block j (from the call's input state), or (ADJ) the
+// pre-rotated adjoint before block j (from the gradients of the final state, blocks of segment 0
+// excluded).  The walks then read one of them instead of combining them all, each unit its own.
+// One thread per mode and four head dims; the loads are issued eight summaries at a time.
+template <int D, int MP, bool ADJ>
+__global__ __launch_bounds__(kThreads) void bwd16_scan_kernel(BwdArgs a)
+{
+    constexpr int PER = 2 * MP * D / 4, AHEAD = 8;
+    const long long gid = (long long)blockIdx.x * kThreads + threadIdx.x;
+    if (gid >= (long long)a.B * a.H * PER) return;
+    const int bh = (int)(gid / PER), h = bh % a.H, e = (int)(gid % PER);
+    const int side = e / (PER / 2), m = e % (PER / 2) / (D / 4), d = 4 * (e % (D / 4));
+    const float* E1 = a.E32 + ((size_t)h * (kChunk + 1) + 1) * 2 * MP;
+    const float* in = ADJ ? (side ? a.gv_out : a.gk_out) : (side ? a.sv_in : a.sk_in);
+    floatx4 zr = zero4(), zi = zero4();
+    if (in && m < a.M) {
+        const floatx4 xr = ld4f(in + (((size_t)bh * 2 + 0) * a.M + m) * D + d);
+        const floatx4 xi = ld4f(in + (((size_t)bh * 2 + 1) * a.M + m) * D + d);
+        const float c1 = E1[m], s1 = E1[MP + m];
+        zr = c1 * xr - s1 * xi;
+        zi = s1 * xr + c1 * xi;
+    }
+    // every block but the sequence's last is cpb full chunks long; the adjoint rotates backwards
+    float cf, sf, cl, sl;
+    bwd_phase(m, (long long)a.cpb * kChunk, a.rperiod[h], cf, sf);
+    bwd_phase(m, (long long)a.L - (long long)(a.nbk - 1) * a.cpb * kChunk, a.rperiod[h], cl, sl);
+    const int first = ADJ ? a.nbk / a.nseg : 0, cnt = a.nbk - first;
+    float* S = (ADJ ? a.asum : a.fsum) + (size_t)bh * a.nbk * 4 * MP * D + (size_t)2 * side * MP * D + (size_t)m * D + d;
+    for (int j0 = 0; j0 < cnt; j0 += AHEAD) {
+        floatx4 sr[AHEAD], si[AHEAD];
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const int i = min(j0 + u, cnt - 1), j = ADJ ? a.nbk - 1 - i : i;
+            sr[u] = ld4f(S + (size_t)j * 4 * MP * D);
+            si[u] = ld4f(S + (size_t)j * 4 * MP * D + (size_t)MP * D);
+        }
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            if (j0 + u >= cnt) continue;
+            const int j = ADJ ? a.nbk - 1 - (j0 + u) : j0 + u;
+            const float c = j == a.nbk - 1 ? cl : cf, s0 = j == a.nbk - 1 ? sl : sf, s = ADJ ? -s0 : s0;
+            const floatx4 nr = c * zr - s * zi + sr[u];
+            zi = s * zr + c * zi + si[u];
+            zr = nr;
+            st4f(S + (size_t)j * 4 * MP * D, zr);
+            st4f(S + (size_t)j * 4 * MP * D + (size_t)MP * D, zi);
+        }
+    }
+}
+
+// Summary blocks per sequence from which the scans run.  Measured on whole calls (us, combined in
+// the walks / scanned), d = M = 64: one sequence of 2000 tokens 177 / 61, 16 of 2000 with 127 slots
+// 265 / 114, 32 of 4096 250 / 191.  At four blocks (the LM layer) the scans would move more bytes
+// than the walks read.
+constexpr int kBwdScanBlocks = 8;
+
+// ---------------------------------------------------------------------------------
 // The reverse walk over one (b, h, segment), bf16.  SUM: adjoint summary only.
 //
 // Eight waves, two per SIMD, in two sides of four.  Side 0 carries what belongs to the keys and
@@ -369,7 +427,8 @@ __global__ __launch_bounds__((Bwd16<D, MP, SP>::NTHR)) void bwd16_kernel(BwdArgs
     floatx4 Z[2][NDT];
     {
         const int m = 16 * mt + r;
-        const float* sin_ = side ? a.sv_in : a.sk_in;
+        const bool scanned = a.nbk >= kBwdScanBlocks;  // summary last_blk is the state
+        const float* sin_ = scanned ? nullptr : side ? a.sv_in : a.sk_in;
         const float c1 = rho1[m], s1 = rho1[MP + m];
 #pragma unroll
         for (int d4 = 0; d4 < NDT; ++d4) {
@@ -381,7 +440,7 @@ __global__ __launch_bounds__((Bwd16<D, MP, SP>::NTHR)) void bwd16_kernel(BwdArgs
             Z[0][d4] = c1 * xr - s1 * xi;
             Z[1][d4] = s1 * xr + c1 * xi;
         }
-        for (int sg = 0; sg <= last_blk; ++sg) {
+        for (int sg = scanned ? last_blk : 0; sg <= last_blk; ++sg) {
             const long long len = (long long)min(a.cpb * C, a.L - sg * a.cpb * C);
             const float* S = a.fsum + ((size_t)bh * a.nbk + sg) * 4 * MP * D + (size_t)2 * side * MP * D;
             float cc, ss;
@@ -401,7 +460,9 @@ __global__ __launch_bounds__((Bwd16<D, MP, SP>::NTHR)) void bwd16_kernel(BwdArgs
     // tile; side 0 Gam'_k, side 1 Gam'_v): Horner over the adjoint summaries of the later segments
     // from rho dLoss/d(final states)
     floatx4 Gm[2][NMT];
-    const float* gout = side ? a.gv_out : a.gk_out;
+    // scanned: summary last_blk + 1 is the adjoint, for every segment but the last
+    const bool gscan = a.nbk >= kBwdScanBlocks && last_blk + 1 < a.nbk;
+    const float* gout = gscan ? nullptr : side ? a.gv_out : a.gk_out;
 #pragma unroll
     for (int m4 = 0; m4 < NMT; ++m4) {
         Gm[0][m4] = Gm[1][m4] = zero4();
@@ -420,7 +481,7 @@ __global__ __launch_bounds__((Bwd16<D, MP, SP>::NTHR)) void bwd16_kernel(BwdArgs
         }
     }
     if constexpr (!SUM) {
-        for (int sg = a.nbk - 1; sg > last_blk; --sg) {
+        for (int sg = gscan ? last_blk + 1 : a.nbk - 1; sg > last_blk; --sg) {
             const long long len = (long long)min(a.cpb * C, a.L - sg * a.cpb * C);
             const float* S = a.asum + ((size_t)bh * a.nbk + sg) * 4 * MP * D + (size_t)2 * side * MP * D;
 #pragma unroll
@@ -838,11 +899,21 @@ hipError_t launch_backward16_shape(const BwdArgs& a, hipStream_t s, void* const*
     const unsigned units = (unsigned)(a.B * a.H);
     hipLaunchKernelGGL((bwd16_fsum_kernel<D, MP>), dim3(2 * units * a.nbk), dim3(kThreads), 0, s, a);
     hipError_t e = hipGetLastError();
+    const dim3 sgrid((unsigned)(((size_t)units * 2 * MP * D / 4 + kThreads - 1) / kThreads));
+    const bool scan = a.nbk >= kBwdScanBlocks;
+    if (e == hipSuccess && scan) {
+        hipLaunchKernelGGL((bwd16_scan_kernel<D, MP, false>), sgrid, dim3(kThreads), 0, s, a);
+        e = hipGetLastError();
+    }
     if (e != hipSuccess || (e = mark(0)) != hipSuccess) return e;
     if (a.nseg > 1) {
         const unsigned sum_blocks = (unsigned)(a.nbk - a.nbk / a.nseg);  // blocks of segments 1..nseg-1
         hipLaunchKernelGGL((bwd16_kernel<D, MP, SP, true>), dim3(units * sum_blocks), dim3(Bwd16<D, MP, SP>::NTHR), 0, s, a);
         if ((e = hipGetLastError()) != hipSuccess) return e;
+        if (scan) {
+            hipLaunchKernelGGL((bwd16_scan_kernel<D, MP, true>), sgrid, dim3(kThreads), 0, s, a);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
     }
     if ((e = mark(1)) != hipSuccess) return e;
     hipLaunchKernelGGL((bwd16_kernel<D, MP, SP, false>), dim3(units * a.nseg), dim3(Bwd16<D, MP, SP>::NTHR), 0, s, a);

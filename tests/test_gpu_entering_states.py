@@ -32,3 +32,19 @@ def test_entering_states(B, H, nch, d, M, S, T):
     sk, sv = (rng.standard_normal((B, H, 2, M, d)).astype(np.float32) for _ in range(2))
     sk[:, :, 1, 0] = sv[:, :, 1, 0] = 0.0
     run_case(q, k, v, T, M, S, torch.bfloat16, t0=100, sk=sk, sv=sv, label=f"{B}x{H}x{L}x{d}")
+
+
+BWD_CASES = [  # B, H, chunks, d, M, S, T: many summary blocks per sequence (scanned), and just too few
+    (1, 2, 20, 64, 64, 64, (127.0, 254.0)),
+    (1, 3, 8, 64, 20, 39, (39.0, 41.5, 78.0)),
+    (1, 3, 7, 32, 16, 31, (31.0, 62.0, 31.0)),
+    (2, 12, 40, 32, 32, 63, tuple(63.0 * (1 + h % 2) for h in range(12))),   # several blocks per segment
+]
+
+
+@pytest.mark.parametrize("B,H,nch,d,M,S,T", BWD_CASES)
+def test_backward_blocks(B, H, nch, d, M, S, T):
+    from test_gpu_backward import run_bwd, tensors
+    (q, k, v, g), (sk, sv, gk, gv) = tensors(nch + M, B, H, 64 * nch - 23, d, M, torch.bfloat16, with_states=True)
+    run_bwd(q, k, v, g, T, M, S, torch.bfloat16, t0=50, sk=sk, sv=sv, gk=gk, gv=gv, label=f"{B}x{H}x{nch} chunks",
+            rows=[(0, 0), (B - 1, H - 1)])
