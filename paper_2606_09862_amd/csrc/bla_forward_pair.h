@@ -56,6 +56,9 @@ template <int D, int MP, int SP> struct Pair {
     static constexpr int NMT = MP / 16, NDT = D / 16, NST = SP / 16;
     static constexpr int KBD = D / 32, KBM = 2 * MP / 32, KBC = C / 32, KBS = SP / 32;
     static constexpr int OWN = (NMT + WPU - 1) / WPU;
+    // With two mode tiles, waves 0, 1 own Z'_k and waves 2, 3 Z'_v of tiles 0, 1; otherwise a wave
+    // owns both states of tiles wl, wl + 4, ...
+    static constexpr bool KV_SPLIT = NMT == 2;
     // Slot rows held in LDS (bla_device.h, slot folding), their tiles and reduction blocks
     static constexpr bool FOLD = slots_folded(SP);
     static constexpr int HP = slot_rows(SP), NHT = HP / 16, KBH = HP / 32;
@@ -212,10 +215,11 @@ __device__ __forceinline__ void pair_write_zv(bf16* ZvT, const PState<D, MP, SP>
 // Step (10) on the wave's owned mode tiles: Z' <- rho^c o (Z' + sum_i conj(rho^i) [k_i | v_i])
 // with K, V ([C][LK], rows past c zero) and the phase table ([C][LE], row-swizzled) read
 // transposed from LDS, and rho^c (cos | sin, float32) from Ec.
+// do_k, do_v: which of the two states the wave owns (uniform).
 template <int D, int MP, int LK, int LE>
 __device__ __forceinline__ void pair_advance(PStateDM<D, MP>& Zk, PStateDM<D, MP>& Zv, const bf16* Ks,
                                              const bf16* Vs, const bf16* sE, const float* Ec, int wl,
-                                             int g, int r)
+                                             int g, int r, bool do_k, bool do_v)
 {
     using F = bf16x8;
     constexpr int NMT = MP / 16, NDT = D / 16, OWN = (NMT + 3) / 4, KBC = kChunk / 32;
@@ -224,8 +228,8 @@ __device__ __forceinline__ void pair_advance(PStateDM<D, MP>& Zk, PStateDM<D, MP
         F ktf[NDT], vtf[NDT];
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
-            ktf[dt] = ld_frag_tr(Ks, LK, 16 * dt, kb, g, r);
-            vtf[dt] = ld_frag_tr(Vs, LK, 16 * dt, kb, g, r);
+            if (do_k) ktf[dt] = ld_frag_tr(Ks, LK, 16 * dt, kb, g, r);
+            if (do_v) vtf[dt] = ld_frag_tr(Vs, LK, 16 * dt, kb, g, r);
         }
 #pragma unroll
         for (int o = 0; o < OWN; ++o) {
@@ -233,12 +237,19 @@ __device__ __forceinline__ void pair_advance(PStateDM<D, MP>& Zk, PStateDM<D, MP
             if (mt < NMT) {
                 const F ecf = ld_frag_tr_sw(sE, LE, 16 * mt, kb, g, r);
                 const F esf = ld_frag_tr_sw(sE, LE, MP + 16 * mt, kb, g, r);
+                if (do_k) {
 #pragma unroll
-                for (int dt = 0; dt < NDT; ++dt) {
-                    Zk[o][0][dt] = mma(ktf[dt], ecf, Zk[o][0][dt]);
-                    Zk[o][1][dt] = mma(ktf[dt], esf, Zk[o][1][dt]);
-                    Zv[o][0][dt] = mma(ecf, vtf[dt], Zv[o][0][dt]);
-                    Zv[o][1][dt] = mma(esf, vtf[dt], Zv[o][1][dt]);
+                    for (int dt = 0; dt < NDT; ++dt) {
+                        Zk[o][0][dt] = mma(ktf[dt], ecf, Zk[o][0][dt]);
+                        Zk[o][1][dt] = mma(ktf[dt], esf, Zk[o][1][dt]);
+                    }
+                }
+                if (do_v) {
+#pragma unroll
+                    for (int dt = 0; dt < NDT; ++dt) {
+                        Zv[o][0][dt] = mma(ecf, vtf[dt], Zv[o][0][dt]);
+                        Zv[o][1][dt] = mma(esf, vtf[dt], Zv[o][1][dt]);
+                    }
                 }
             }
         }
@@ -249,14 +260,21 @@ __device__ __forceinline__ void pair_advance(PStateDM<D, MP>& Zk, PStateDM<D, MP
         if (mt < NMT) {
             const float cc = Ec[16 * mt + r], ss = Ec[MP + 16 * mt + r];
             const floatx4 cv = ld4f(Ec + 16 * mt + 4 * g), sv = ld4f(Ec + MP + 16 * mt + 4 * g);
+            if (do_k) {
 #pragma unroll
-            for (int dt = 0; dt < NDT; ++dt) {
-                const floatx4 kr = Zk[o][0][dt], ki = Zk[o][1][dt];
-                Zk[o][0][dt] = cc * kr - ss * ki;
-                Zk[o][1][dt] = ss * kr + cc * ki;
-                const floatx4 vr = Zv[o][0][dt], vi = Zv[o][1][dt];
-                Zv[o][0][dt] = cv * vr - sv * vi;
-                Zv[o][1][dt] = sv * vr + cv * vi;
+                for (int dt = 0; dt < NDT; ++dt) {
+                    const floatx4 kr = Zk[o][0][dt], ki = Zk[o][1][dt];
+                    Zk[o][0][dt] = cc * kr - ss * ki;
+                    Zk[o][1][dt] = ss * kr + cc * ki;
+                }
+            }
+            if (do_v) {
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt) {
+                    const floatx4 vr = Zv[o][0][dt], vi = Zv[o][1][dt];
+                    Zv[o][0][dt] = cv * vr - sv * vi;
+                    Zv[o][1][dt] = sv * vr + cv * vi;
+                }
             }
         }
     }
@@ -724,6 +742,9 @@ __global__ __launch_bounds__((256 * Pair<D, MP, SP>::U)) void forward_pair_kerne
     const int ut = tid & 255;                      // thread index within the unit
     const int g = (tid & 63) >> 4, r = tid & 15;
     const int tt = u == 0 ? wl : NT - 1 - wl;      // token tile of this wave's chain
+    // first owned mode tile, and which states of the owned tiles are the wave's
+    const int ow = P::KV_SPLIT ? wl % 2 : wl;
+    const bool own_k = !P::KV_SPLIT || wl < 2, own_v = !P::KV_SPLIT || wl >= 2;
     const int h = blockIdx.y;
     const int per_head = a.B * a.nseg;
     const int v_unit = blockIdx.x * P::U + u;
@@ -809,18 +830,18 @@ __global__ __launch_bounds__((256 * Pair<D, MP, SP>::U)) void forward_pair_kerne
     const bool entered = a.entered && seg > 0;  // the state is in summary slot seg - 1
 #pragma unroll
     for (int o = 0; o < OWN; ++o) {
-        const int mt = wl + P::WPU * o;
+        const int mt = ow + P::WPU * o;
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
             Zk[o][0][dt] = Zk[o][1][dt] = Zv[o][0][dt] = Zv[o][1][dt] = zero4();
             if (mt < NMT && active && !entered) {
                 const int m = 16 * mt + r;
                 floatx4 kr = zero4(), ki = zero4(), vr = zero4(), vi = zero4();
-                if (a.sk_in && m < a.M) {
+                if (a.sk_in && own_k && m < a.M) {
                     kr = ld4f(a.sk_in + (((size_t)bh * 2 + 0) * a.M + m) * D + 16 * dt + 4 * g);
                     ki = ld4f(a.sk_in + (((size_t)bh * 2 + 1) * a.M + m) * D + 16 * dt + 4 * g);
                 }
-                if (a.sv_in) {
+                if (a.sv_in && own_v) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const int mv = 16 * mt + 4 * g + e;
@@ -843,14 +864,14 @@ __global__ __launch_bounds__((256 * Pair<D, MP, SP>::U)) void forward_pair_kerne
         const float* S = a.summ + ((size_t)bh * a.nbs + seg - 1) * 4 * MP * D;
 #pragma unroll
         for (int o = 0; o < OWN; ++o) {
-            const int mt = wl + P::WPU * o;
+            const int mt = ow + P::WPU * o;
             if (mt < NMT) {
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
                     for (int p = 0; p < 2; ++p) {
-                        Zk[o][p][dt] = ld4f(S + sum_tile<D, MP>(p, mt, dt) + 4 * (tid & 63));
-                        Zv[o][p][dt] = ld4f(S + sum_tile<D, MP>(2 + p, mt, dt) + 4 * (tid & 63));
+                        if (own_k) Zk[o][p][dt] = ld4f(S + sum_tile<D, MP>(p, mt, dt) + 4 * (tid & 63));
+                        if (own_v) Zv[o][p][dt] = ld4f(S + sum_tile<D, MP>(2 + p, mt, dt) + 4 * (tid & 63));
                     }
             }
         }
@@ -867,28 +888,34 @@ __global__ __launch_bounds__((256 * Pair<D, MP, SP>::U)) void forward_pair_kerne
             const float* Sj = Sb + (size_t)min(j, nblk - 1) * 4 * MP * D;
 #pragma unroll
             for (int o = 0; o < OWN; ++o) {
-                const int mt = min(wl + P::WPU * o, NMT - 1);
+                const int mt = min(ow + P::WPU * o, NMT - 1);
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-                    for (int pp = 0; pp < 4; ++pp) dst[o][dt][pp] = ld4f(Sj + sum_tile<D, MP>(pp, mt, dt) + 4 * (tid & 63));
+                    for (int pp = 0; pp < (P::KV_SPLIT ? 2 : 4); ++pp)
+                        dst[o][dt][pp] = ld4f(Sj + sum_tile<D, MP>(pp + (P::KV_SPLIT && own_v ? 2 : 0), mt, dt) + 4 * (tid & 63));
             }
         };
         auto combine = [&](const floatx4 (&src)[OWN][NDT][4]) {
 #pragma unroll
             for (int o = 0; o < OWN; ++o) {
-                const int mt = wl + P::WPU * o;
+                const int mt = ow + P::WPU * o;
                 if (mt < NMT) {
                     const float cc = rb[16 * mt + r], ss = rb[MP + 16 * mt + r];
                     const floatx4 cv = ld4f(rb + 16 * mt + 4 * g), sv = ld4f(rb + MP + 16 * mt + 4 * g);
 #pragma unroll
                     for (int dt = 0; dt < NDT; ++dt) {
-                        const floatx4 kr = Zk[o][0][dt], ki = Zk[o][1][dt];
-                        Zk[o][0][dt] = cc * kr - ss * ki + src[o][dt][0];
-                        Zk[o][1][dt] = ss * kr + cc * ki + src[o][dt][1];
-                        const floatx4 vr = Zv[o][0][dt], vi = Zv[o][1][dt];
-                        Zv[o][0][dt] = cv * vr - sv * vi + src[o][dt][2];
-                        Zv[o][1][dt] = sv * vr + cv * vi + src[o][dt][3];
+                        constexpr int V = P::KV_SPLIT ? 0 : 2;  // where a summary's value parts were loaded
+                        if (own_k) {
+                            const floatx4 kr = Zk[o][0][dt], ki = Zk[o][1][dt];
+                            Zk[o][0][dt] = cc * kr - ss * ki + src[o][dt][0];
+                            Zk[o][1][dt] = ss * kr + cc * ki + src[o][dt][1];
+                        }
+                        if (own_v) {
+                            const floatx4 vr = Zv[o][0][dt], vi = Zv[o][1][dt];
+                            Zv[o][0][dt] = cv * vr - sv * vi + src[o][dt][V];
+                            Zv[o][1][dt] = sv * vr + cv * vi + src[o][dt][V + 1];
+                        }
                     }
                 }
             }
@@ -924,8 +951,8 @@ __global__ __launch_bounds__((256 * Pair<D, MP, SP>::U)) void forward_pair_kerne
     F qf[P::KBD];
     load_q(qf, 0);
     stage_chunk(st, 0);
-    pair_write_zk<D, MP, SP>(ZkT, Zk, wl, g, r);
-    pair_write_zv<D, MP, SP>(ZvT, Zv, wl, g, r);
+    if (own_k) pair_write_zk<D, MP, SP>(ZkT, Zk, ow, g, r);
+    if (own_v) pair_write_zv<D, MP, SP>(ZvT, Zv, ow, g, r);
     {
         const int c0 = nch > 0 ? min(C, a.L - ch0 * C) : 0;
         if (c0 == C)
@@ -1180,14 +1207,14 @@ __global__ __launch_bounds__((256 * Pair<D, MP, SP>::U)) void forward_pair_kerne
         // ================= phase 1 (independent of the chain): step (10) on the owned mode tiles
         if (live) {
             const float* Ec = sRho + (c == C ? 2 * MP : 4 * MP);  // a chunk shorter than C is the last one
-            pair_advance<D, MP, P::LK, P::LE>(Zk, Zv, Ks, Vs, sE, Ec, wl, g, r);
+            pair_advance<D, MP, P::LK, P::LE>(Zk, Zv, Ks, Vs, sE, Ec, ow, g, r, own_k, own_v);
         }
         __syncthreads();  // chunk n and its published state no longer read
 
         // ================= phase 2: publish the state of chunk n + 1, stage chunk n + 1
         if (live) {
-            pair_write_zk<D, MP, SP>(ZkT, Zk, wl, g, r);
-            pair_write_zv<D, MP, SP>(ZvT, Zv, wl, g, r);
+            if (own_k) pair_write_zk<D, MP, SP>(ZkT, Zk, ow, g, r);
+            if (own_v) pair_write_zv<D, MP, SP>(ZvT, Zv, ow, g, r);
         }
         const int cn = n + 1 < nch ? min(C, a.L - (tok0 + C)) : 0;
         if (cn == C)
@@ -1203,19 +1230,19 @@ __global__ __launch_bounds__((256 * Pair<D, MP, SP>::U)) void forward_pair_kerne
     if (active && seg == a.nseg - 1) {
 #pragma unroll
         for (int o = 0; o < OWN; ++o) {
-            const int mt = wl + P::WPU * o;
+            const int mt = ow + P::WPU * o;
             if (mt < NMT) {
                 const int m = 16 * mt + r;
                 const float c1 = E1[m], s1 = E1[MP + m];
                 const floatx4 cv = ld4f(E1 + 16 * mt + 4 * g), sv = ld4f(E1 + MP + 16 * mt + 4 * g);
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt) {
-                    if (a.sk_out && m < a.M) {
+                    if (a.sk_out && own_k && m < a.M) {
                         const floatx4 re = Zk[o][0][dt], im = Zk[o][1][dt];
                         st4f(a.sk_out + (((size_t)bh * 2 + 0) * a.M + m) * D + 16 * dt + 4 * g, c1 * re + s1 * im);
                         st4f(a.sk_out + (((size_t)bh * 2 + 1) * a.M + m) * D + 16 * dt + 4 * g, c1 * im - s1 * re);
                     }
-                    if (a.sv_out) {
+                    if (a.sv_out && own_v) {
                         const floatx4 re = Zv[o][0][dt], im = Zv[o][1][dt];
                         const floatx4 nr = cv * re + sv * im, ni = cv * im - sv * re;
 #pragma unroll
