@@ -40,7 +40,8 @@
  *     device memory: scratch space (tables, per-block partial states) lives in the
  *     caller's workspace, sized by bla_workspace_size / bla_step_workspace_size.  Two
  *     exceptions, both outside the operator's own kernels: the first bla_layer_forward
- *     on a device creates a hipBLASLt handle (hipBLASLt allocates its own memory), and
+ *     on a device whose projections are large enough for the vendor library creates a
+ *     hipBLASLt handle (hipBLASLt allocates its own memory), and
  *     bla_forward_noalloc's workspace is a fixed device array of the library's code
  *     object (allocated with the module, once per device).
  *   - Calls are asynchronous on `stream` (a hipStream_t; NULL = default stream).
@@ -287,13 +288,13 @@ bla_status bla_backward_timed(const bla_params* p, const double* T, const void* 
  *     [q | k | v] = x W_qkv,   o = BLA(q, k, v),   y = o W_o
  * with x, y [B, L, D] row-major, W_qkv [D, 3D] (columns h d_k .. h d_k + d_k - 1 of block 0,
  * 1, 2 are head h's query, key and value projections), W_o [D, D] (row h d_k + e takes element
- * e of head h's output), all bf16; the products accumulate in float32 (hipBLASLt) and q, k, v
- * and o are rounded to bf16 between the steps.  p describes the operator (p->d_k = p->d_v is
+ * e of head h's output), all bf16; the products accumulate in float32 (the library's own kernel
+ * for D <= 512 and small products, hipBLASLt for large ones) and q, k, v and o are rounded to bf16 between the steps.  p describes the operator (p->d_k = p->d_v is
  * the head width, p->L the tokens); states as for bla_forward.  The operator reads q, k, v in
  * place from the projection output [B, L, 3, H, d_k] and writes o in place as [B, L, H, d_k],
  * the output projection's input.  The workspace holds those two tensors, the operator's
  * workspace and 32 MB of GEMM scratch.  The first call on
- * a device creates a hipBLASLt handle that lives until the process ends.  Errors as for
+ * a device with a product for hipBLASLt creates a handle that lives until the process ends.  Errors as for
  * bla_forward; a failing GEMM is BLA_ERR_HIP.
  */
 size_t bla_layer_workspace_size(const bla_params* p);
