@@ -90,6 +90,14 @@ void tables_record(int dev, const void* ws, uint64_t key)
     g_table_next = (g_table_next + 1) % kTableRecords;
 }
 
+// The workspace holds no tables any more: a call that built none of its own has written it.
+void tables_forget(int dev, const void* ws)
+{
+    std::lock_guard<std::mutex> lk(g_table_mu);
+    for (int i = 0; i < kTableRecords; ++i)
+        if (g_table_rec[i].ws == ws && g_table_rec[i].dev == dev) g_table_rec[i].ws = nullptr;
+}
+
 bool aligned16(const void* ptr) { return ((uintptr_t)ptr & 15u) == 0; }
 
 // Shape checks shared by every entry point (no pointers).
@@ -708,6 +716,12 @@ static bla_status decay_forward_impl(const bla_params* p, const double* T, const
     if (!mark(0)) return BLA_ERR_HIP;
     DecayPeriods periods;
     if ((st = decay_periods(pl, T, ws, s, p->reuse_tables, &periods)) != BLA_OK) return st;
+    if (!periods.tab) {
+        // the schedules and summaries below lie where another entry point's tables may have been
+        int dev = -1;
+        if (hipGetDevice(&dev) != hipSuccess) return BLA_ERR_HIP;
+        tables_forget(dev, ws);
+    }
     DecayArgs a;
     memset(&a, 0, sizeof(a));
     a.q = q;

@@ -48,3 +48,20 @@ def test_backward_blocks(B, H, nch, d, M, S, T):
     (q, k, v, g), (sk, sv, gk, gv) = tensors(nch + M, B, H, 64 * nch - 23, d, M, torch.bfloat16, with_states=True)
     run_bwd(q, k, v, g, T, M, S, torch.bfloat16, t0=50, sk=sk, sv=sv, gk=gk, gv=gv, label=f"{B}x{H}x{nch} chunks",
             rows=[(0, 0), (B - 1, H - 1)])
+
+
+def test_decay_call_between_table_reuses():
+    """A decay forward builds no tables but writes its schedules into the workspace: a forward that
+    asks for the tables an earlier one left there must build them again."""
+    from test_gpu_parity import _bla, to_dev
+    bla = _bla()
+    B, H, L, d, M, S, T = 1, 4, 64 * 12, 64, 32, 32, (63.0, 126.0, 70.5, 90.0)
+    q, k, v = (to_dev(x, torch.bfloat16) for x in gauss(5, B, H, L, d, torch.bfloat16))
+    p = bla.make_params(B, H, L, d, M, S, torch.bfloat16)
+    ws = torch.empty(max(bla.workspace_size(p), bla.decay_workspace_size(p)), dtype=torch.uint8, device="cuda")
+    first = bla.forward(q, k, v, T, M, S, workspace=ws)
+    bla.decay_forward(q, k, v, T, M, S, workspace=ws)
+    again = bla.forward(q, k, v, T, M, S, workspace=ws, reuse_tables=True)
+    torch.cuda.synchronize()
+    for a, b in zip(first, again):
+        assert torch.equal(a, b)
