@@ -219,9 +219,6 @@ void make_plan_for(const bla_params* p, bool step, bool one_per_cu, Plan* pl)
     pl->off_trig = off;   off = align_up(off + 2 * SP * 4);
     pl->off_rperiod = off; off = align_up(off + H * 8);
     pl->off_period = off; off = align_up(off + H * 8);
-    pl->off_summ = off;   off = align_up(off + (size_t)units * pl->nbs * pl->unit_floats * 4);
-    const size_t ncarry = pl->pair ? 0 : (size_t)(pl->nseg - 1);  // the pair kernel needs no carries
-    pl->off_carry = off;  off = align_up(off + (size_t)units * ncarry * pl->unit_floats * 4);
     // the bf16 d = M = 128 forward kernel with 64 or 128 slots reads its tables as fragments
     pl->fragtab = !step && pl->bf16 && !pl->pair && pl->C == kChunk && pl->D == 128 && pl->MP == 128 &&
                   (pl->SP == 64 || pl->SP == 128);
@@ -232,6 +229,10 @@ void make_plan_for(const bla_params* p, bool step, bool one_per_cu, Plan* pl)
     pl->off_fEbar = off;  off = align_up(off + fh);
     pl->off_fErev = off;  off = align_up(off + fh);
     pl->off_fTw = off;    off = align_up(off + fh);
+    // every table lies before the scratch, so that where they lie depends only on what table_key covers
+    pl->off_summ = off;   off = align_up(off + (size_t)units * pl->nbs * pl->unit_floats * 4);
+    const size_t ncarry = pl->pair ? 0 : (size_t)(pl->nseg - 1);  // the pair kernel needs no carries
+    pl->off_carry = off;  off = align_up(off + (size_t)units * ncarry * pl->unit_floats * 4);
     pl->total = off;
 }
 
@@ -249,11 +250,9 @@ void make_plan(const bla_params* p, bool step, Plan* pl)
     }
 }
 
-// step: a decode step needs the phase rows j = 0, 1 only.  reuse: skip the launch when the
-// library's record says this workspace already holds exactly these tables.
-bla_status build_tables(const Plan& pl, const double* T, char* ws, hipStream_t s, bool step, int reuse)
+// Key of a plan's tables: everything that their contents and places in the workspace depend on.
+uint64_t table_key(const Plan& pl, const double* T, bool step)
 {
-    // key: everything the tables' contents and layout depend on
     int32_t f[14] = {pl.H, pl.M, pl.S, pl.MP, pl.SP, pl.C, pl.bf16, pl.anchor, pl.pair, step ? 2 : pl.C + 1,
                      pl.cpb * pl.C, 0, step ? 0 : pl.fragtab, 0};
     const float tab_scale = pl.pair ? 1.f : pl.scale;
@@ -263,6 +262,14 @@ bla_status build_tables(const Plan& pl, const double* T, char* ws, hipStream_t s
         const double tmin = 2.0 * pl.M - 1.0, Tc = T[h] < tmin ? tmin : T[h];
         key = fnv_mix(key, &Tc, sizeof(Tc));
     }
+    return key;
+}
+
+// step: a decode step needs the phase rows j = 0, 1 only.  reuse: skip the launch when the
+// library's record says this workspace already holds exactly these tables.
+bla_status build_tables(const Plan& pl, const double* T, char* ws, hipStream_t s, bool step, int reuse)
+{
+    const uint64_t key = table_key(pl, T, step);
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return BLA_ERR_HIP;
     if (reuse && tables_recorded(dev, ws, key)) return BLA_OK;

@@ -1,0 +1,52 @@
+// Host-side view of the library's internals for the CPU tests: the launch plans (bla_api.hip) and
+// the slot order of the folded kernels (bla_device.h).  Compiled for the host only.
+#include <stdio.h>
+#include <stdlib.h>
+
+#include "bla_api.hip"
+#include "bla_device.h"
+
+// plan: reads lines "form B H L d M S bf16 chunk anchor", form f (forward), b (backward) or s (step),
+// with T = (1 + h mod 2)(2M - 1); prints the table key, where the tables and the scratch lie, and the
+// work split.
+static int plans()
+{
+    char form;
+    int B, H, L, d, M, S, bf16, chunk, anchor;
+    while (scanf(" %c %d %d %d %d %d %d %d %d %d", &form, &B, &H, &L, &d, &M, &S, &bf16, &chunk, &anchor) == 10) {
+        bla_params p;
+        memset(&p, 0, sizeof(p));
+        p.B = B, p.H = H, p.L = L, p.d_k = p.d_v = d, p.M = M, p.S = S, p.chunk = chunk;
+        p.io_dtype = bf16 ? BLA_BF16 : BLA_F32, p.phase_anchor = anchor;
+        const bool step = form == 's';
+        if ((form == 'b' ? check_backward_shape(&p) : check_shape(&p, step)) != BLA_OK) {
+            printf("unsupported\n");
+            continue;
+        }
+        double* T = (double*)malloc(sizeof(double) * H);
+        for (int h = 0; h < H; ++h) T[h] = (1 + h % 2) * (2.0 * M - 1.0);
+        Plan pl;
+        if (form == 'b') {
+            BwdPlan bp;
+            make_bwd_plan(&p, &bp);
+            pl = bp.pl;
+        } else {
+            make_plan(&p, step, &pl);
+        }
+        printf("key %llu summ %zu total %zu nseg %d cps %d pair %d fragtab %d tables", (unsigned long long)table_key(pl, T, step),
+               pl.off_summ, pl.total, pl.nseg, pl.cps, pl.pair, pl.fragtab);
+        const size_t offs[] = {pl.off_E32, pl.off_EbarT, pl.off_ErevT, pl.off_Etab, pl.off_ABs, pl.off_ABm, pl.off_theta,
+                               pl.off_rotblk, pl.off_trig, pl.off_rperiod, pl.off_period, pl.off_fABs, pl.off_fABm,
+                               pl.off_fEtab, pl.off_fEbar, pl.off_fErev, pl.off_fTw};
+        for (size_t x : offs) printf(" %zu", x);
+        printf("\n");
+        free(T);
+    }
+    return 0;
+}
+
+int main(int argc, char** argv)
+{
+    if (argc == 2 && !strcmp(argv[1], "plan")) return plans();
+    return 2;
+}
