@@ -100,8 +100,10 @@ typedef struct {
                             last built there (entry point, every field of *p that the tables
                             depend on, and the periods T); a call with reuse_tables = 1 skips
                             the table kernel only when that record matches, and builds the
-                            tables otherwise.  The caller guarantees that nothing else has
-                            written the workspace since that call (a workspace freed and
+                            tables otherwise.  A record ends with the next call of any entry
+                            point whose own workspace covers the tables.  The caller guarantees
+                            that nothing but the library's calls has written the workspace
+                            since that call (a workspace freed and
                             allocated again at the same address holds stale bytes: pass 0
                             then).  Any value other than 0 or 1 is BLA_ERR_INVALID_ARG.     */
 } bla_params;

@@ -50,12 +50,15 @@ int device_cu_count()
     return n;
 }
 
-// Record of the tables last built into each workspace: (device, workspace address) -> key of
-// the tables' contents.  A call with reuse_tables = 1 skips the table kernel when the record
-// of its workspace matches its key.  A fixed ring of records; the oldest is overwritten.
+// Record of the tables built into workspaces: (device, workspace address) -> the bytes that they take
+// from there and the key of their contents.  A call with reuse_tables = 1 skips the table kernel when
+// the record of its workspace matches its key.  Every call that writes a workspace drops the
+// records of the tables that it writes over, wherever their own workspaces begin (a layer's operator
+// has its workspace inside the layer's).  A fixed ring of records; the oldest is overwritten.
 struct TableRecord {
     int dev;
-    const void* ws;
+    const char* ws;
+    size_t bytes;
     uint64_t key;
 };
 constexpr int kTableRecords = 64;
@@ -70,32 +73,29 @@ uint64_t fnv_mix(uint64_t h, const void* data, size_t n)
     return h;
 }
 
-bool tables_recorded(int dev, const void* ws, uint64_t key)
+// The bytes [ws, ws + n) are about to be written: drops every record of tables in them but that of
+// the call's own tables (`own` at ws, if not null).  Returns whether that record exists.
+bool tables_claim(int dev, const char* ws, size_t n, const uint64_t* own)
 {
     std::lock_guard<std::mutex> lk(g_table_mu);
-    for (int i = 0; i < kTableRecords; ++i)
-        if (g_table_rec[i].ws == ws && g_table_rec[i].dev == dev) return g_table_rec[i].key == key;
-    return false;
+    bool found = false;
+    for (TableRecord& r : g_table_rec) {
+        if (!r.ws || r.dev != dev) continue;
+        if (own && r.ws == ws && r.key == *own)
+            found = true;
+        else if ((uintptr_t)r.ws < (uintptr_t)ws + n && (uintptr_t)ws < (uintptr_t)r.ws + r.bytes)
+            r.ws = nullptr;
+    }
+    return found;
 }
 
-void tables_record(int dev, const void* ws, uint64_t key)
+void tables_record(int dev, const char* ws, size_t bytes, uint64_t key)
 {
     std::lock_guard<std::mutex> lk(g_table_mu);
-    for (int i = 0; i < kTableRecords; ++i)
-        if (g_table_rec[i].ws == ws && g_table_rec[i].dev == dev) {
-            g_table_rec[i].key = key;
-            return;
-        }
-    g_table_rec[g_table_next] = TableRecord{dev, ws, key};
+    for (const TableRecord& r : g_table_rec)
+        if (r.ws == ws && r.dev == dev && r.key == key) return;  // built again
+    g_table_rec[g_table_next] = TableRecord{dev, ws, bytes, key};
     g_table_next = (g_table_next + 1) % kTableRecords;
-}
-
-// The workspace holds no tables any more: a call that built none of its own has written it.
-void tables_forget(int dev, const void* ws)
-{
-    std::lock_guard<std::mutex> lk(g_table_mu);
-    for (int i = 0; i < kTableRecords; ++i)
-        if (g_table_rec[i].ws == ws && g_table_rec[i].dev == dev) g_table_rec[i].ws = nullptr;
 }
 
 bool aligned16(const void* ptr) { return ((uintptr_t)ptr & 15u) == 0; }
@@ -266,13 +266,14 @@ uint64_t table_key(const Plan& pl, const double* T, bool step)
 }
 
 // step: a decode step needs the phase rows j = 0, 1 only.  reuse: skip the launch when the
-// library's record says this workspace already holds exactly these tables.
-bla_status build_tables(const Plan& pl, const double* T, char* ws, hipStream_t s, bool step, int reuse)
+// library's record says this workspace already holds exactly these tables.  n: the bytes of the
+// workspace that the call writes.
+bla_status build_tables(const Plan& pl, const double* T, char* ws, size_t n, hipStream_t s, bool step, int reuse)
 {
     const uint64_t key = table_key(pl, T, step);
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return BLA_ERR_HIP;
-    if (reuse && tables_recorded(dev, ws, key)) return BLA_OK;
+    if (tables_claim(dev, ws, n, &key) && reuse) return BLA_OK;
     for (int h0 = 0; h0 < pl.H; h0 += kMaxHeadsPerTableLaunch) {
         TableArgs a;
         memset(&a, 0, sizeof(a));
@@ -325,18 +326,25 @@ bla_status build_tables(const Plan& pl, const double* T, char* ws, hipStream_t s
         fa.SP = pl.SP;
         if (launch_fragtab(fa, s) != hipSuccess) return BLA_ERR_HIP;
     }
-    tables_record(dev, ws, key);
+    tables_record(dev, ws, pl.off_summ, key);
     return BLA_OK;
 }
 
 // The heads' clamped periods for the decay kernels, with the table kernel only where there are
-// more of them than travel with a launch.
-bla_status decay_periods(const Plan& pl, const double* T, char* ws, hipStream_t s, int reuse, DecayPeriods* out)
+// more of them than travel with a launch.  n: the bytes of the workspace that the call writes if it
+// builds tables; other: those that it writes if it builds none.
+bla_status decay_periods(const Plan& pl, const double* T, char* ws, size_t n, size_t other, hipStream_t s, int reuse,
+                         DecayPeriods* out)
 {
     memset(out, 0, sizeof(*out));
     if (pl.H > kMaxHeadsPerTableLaunch) {
         out->tab = (const double*)(ws + pl.off_period);
-        return build_tables(pl, T, ws, s, true, reuse);
+        return build_tables(pl, T, ws, n, s, true, reuse);
+    }
+    if (other > 0) {
+        int dev = -1;
+        if (hipGetDevice(&dev) != hipSuccess) return BLA_ERR_HIP;
+        tables_claim(dev, ws, other, nullptr);
     }
     for (int h = 0; h < pl.H; ++h) {
         const double tmin = 2.0 * pl.M - 1.0;
@@ -550,7 +558,7 @@ static bla_status forward_impl(const bla_params* p, const double* T, const void*
         return !events || !events[i] || hipEventRecord((hipEvent_t)events[i], s) == hipSuccess;
     };
     if (!mark(0)) return BLA_ERR_HIP;
-    if ((st = build_tables(pl, T, ws, s, false, p->reuse_tables)) != BLA_OK) return st;
+    if ((st = build_tables(pl, T, ws, pl.total, s, false, p->reuse_tables)) != BLA_OK) return st;
     if (!mark(1)) return BLA_ERR_HIP;
 
     FwdArgs a;
@@ -649,7 +657,7 @@ bla_status bla_step(const bla_params* p, const double* T, const void* q, const v
     if (!workspace || workspace_bytes < pl.total || !aligned16(workspace)) return BLA_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)workspace;
-    if ((st = build_tables(pl, T, ws, s, true, p->reuse_tables)) != BLA_OK) return st;
+    if ((st = build_tables(pl, T, ws, pl.total, s, true, p->reuse_tables)) != BLA_OK) return st;
     StepArgs a;
     memset(&a, 0, sizeof(a));
     a.q = q;
@@ -722,13 +730,7 @@ static bla_status decay_forward_impl(const bla_params* p, const double* T, const
     };
     if (!mark(0)) return BLA_ERR_HIP;
     DecayPeriods periods;
-    if ((st = decay_periods(pl, T, ws, s, p->reuse_tables, &periods)) != BLA_OK) return st;
-    if (!periods.tab) {
-        // the schedules and summaries below lie where another entry point's tables may have been
-        int dev = -1;
-        if (hipGetDevice(&dev) != hipSuccess) return BLA_ERR_HIP;
-        tables_forget(dev, ws);
-    }
+    if ((st = decay_periods(pl, T, ws, dp.total, dp.total, s, p->reuse_tables, &periods)) != BLA_OK) return st;
     DecayArgs a;
     memset(&a, 0, sizeof(a));
     a.q = q;
@@ -834,7 +836,7 @@ bla_status bla_decay_step(const bla_params* p, const double* T, const void* q, c
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)workspace;
     DecayPeriods periods;
-    if ((st = decay_periods(pl, T, ws, s, p->reuse_tables, &periods)) != BLA_OK) return st;
+    if ((st = decay_periods(pl, T, ws, pl.total, 0, s, p->reuse_tables, &periods)) != BLA_OK) return st;
     DecayStepArgs a;
     memset(&a, 0, sizeof(a));
     a.q = q;
@@ -903,7 +905,7 @@ static bla_status backward_impl(const bla_params* p, const double* T, const void
         return !events || !events[i] || hipEventRecord((hipEvent_t)events[i], s) == hipSuccess;
     };
     if (!mark(0)) return BLA_ERR_HIP;
-    if ((st = build_tables(pl, T, ws, s, false, p->reuse_tables)) != BLA_OK) return st;
+    if ((st = build_tables(pl, T, ws, bp.total, s, false, p->reuse_tables)) != BLA_OK) return st;
     if (!mark(1)) return BLA_ERR_HIP;
     BwdArgs a;
     memset(&a, 0, sizeof(a));
@@ -970,6 +972,14 @@ bla_status bla_backward_timed(const bla_params* p, const double* T, const void* 
 }  // extern "C"
 
 namespace bla {
+
+bool tables_overwritten(const void* ws, size_t n)
+{
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    tables_claim(dev, (const char*)ws, n, nullptr);
+    return true;
+}
 
 bla_status forward_strided(const bla_params* p, const double* T, const void* q, const void* k, const void* v,
                            const long long* in_strides, const float* state_k_in, const float* state_v_in, void* o,

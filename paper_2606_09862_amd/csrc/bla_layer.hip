@@ -152,6 +152,8 @@ static bla_status layer_impl(const bla_params* p, const double* T, const void* x
     const long long in_strides[3] = {L * 3 * D, d, 3 * D};  // [B, L, 3, H, d]
     const long long out_strides[3] = {L * D, d, D};         // [B, L, H, d]
 
+    // the projections' tensors and scratch; the operator answers for its own workspace between them
+    if (!tables_overwritten(ws, lp.off_fwd) || !tables_overwritten(gws, kGemmWorkspace)) return BLA_ERR_HIP;
     if (!mark(0)) return BLA_ERR_HIP;
     if (!gemm_rowmajor((const bf16*)x, (const bf16*)w_qkv, qkv, tok, 3 * D, D, gws, kGemmWorkspace, s))
         return BLA_ERR_HIP;

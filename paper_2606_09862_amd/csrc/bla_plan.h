@@ -318,6 +318,10 @@ bla_status forward_strided(const bla_params* p, const double* T, const void* q, 
                            const long long* in_strides, const float* state_k_in, const float* state_v_in, void* o,
                            const long long* out_strides, float* state_k_out, float* state_v_out, void* workspace,
                            size_t workspace_bytes, void* stream, void* const* events);
+// The caller is about to write n bytes at ws: the tables recorded there are no longer kept.  False if
+// the runtime does not name the current device.
+bool tables_overwritten(const void* ws, size_t n);
+
 // Sequence units per workgroup of the bf16 pair kernel (0: the one-unit forward kernel runs).
 int forward_units_per_wg(int bf16, int D, int MP, int SP);
 

@@ -45,8 +45,33 @@ static int plans()
     return 0;
 }
 
+// records: reads lines "build dev at bytes key" (a call whose tables, of `bytes` at address `at`, are
+// built; it writes nothing else), "keep dev at n key" (a call that writes n bytes and would keep its
+// tables; prints whether they are there) and "write dev at n" (one without tables).
+static int records()
+{
+    char op[8];
+    int dev;
+    unsigned long long at, n, key;
+    while (scanf(" %7s %d %llu %llu", op, &dev, &at, &n) == 4) {
+        if (!strcmp(op, "write")) {
+            tables_claim(dev, (const char*)at, n, nullptr);
+            continue;
+        }
+        if (scanf("%llu", &key) != 1) return 1;
+        const uint64_t k = key;
+        const bool found = tables_claim(dev, (const char*)at, n, &k);
+        if (!strcmp(op, "keep"))
+            printf("%d\n", found);
+        else
+            tables_record(dev, (const char*)at, n, k);
+    }
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
+    if (argc == 2 && !strcmp(argv[1], "records")) return records();
     if (argc == 2 && !strcmp(argv[1], "plan")) return plans();
     return 2;
 }
