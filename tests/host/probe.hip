@@ -69,8 +69,22 @@ static int records()
     return 0;
 }
 
+// slots: for every padded count SP of the folded kernels and slot count S that pads to it, a line "SP S"
+// and the slots of the SP folded entries.
+static int slots()
+{
+    for (int SP = 64; SP <= 256; SP *= 2)
+        for (int S = SP / 2 + 1; S <= SP; ++S) {
+            printf("%d %d", SP, S);
+            for (int i = 0; i < SP; ++i) printf(" %d", folded_slot(i, S, SP));
+            printf("\n");
+        }
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
+    if (argc == 2 && !strcmp(argv[1], "slots")) return slots();
     if (argc == 2 && !strcmp(argv[1], "records")) return records();
     if (argc == 2 && !strcmp(argv[1], "plan")) return plans();
     return 2;

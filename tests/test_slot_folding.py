@@ -9,6 +9,7 @@ import pytest
 import torch
 
 import oracle
+from host_probe import run
 
 
 def folded_slot(i, S, SP):
@@ -20,6 +21,13 @@ def folded_slot(i, S, SP):
     if s == 0:
         return HP if S == SP else None
     return S - s if 2 * s < S else None
+
+
+def test_the_library_orders_the_slots_so():
+    lines = [list(map(int, line.split())) for line in run("slots")]
+    assert len(lines) == 32 + 64 + 128
+    for SP, S, *slots in lines:
+        assert slots == [-1 if (x := folded_slot(i, S, SP)) is None else x for i in range(SP)], (SP, S)
 
 
 @pytest.mark.parametrize("SP", [64, 128, 256])
@@ -66,14 +74,23 @@ CASES = [  # dtype, d, M, S, anchor
 ]
 
 
-@pytest.mark.gpu
-@pytest.mark.parametrize("dtype,d,M,S,anchor", CASES)
-def test_forward(dtype, d, M, S, anchor):
+def anchored_slots(state, T, M, S, pos):
+    """Slot states [B,H,S,d] at position pos from mode states [B,H,2,M,d] (Sec. 3.3)."""
+    m = np.arange(M)
+    c = np.where(m == 0, 1.0, 2.0) / (2 * M - 1)
+    out = []
+    for h, Th in enumerate(T):
+        ph = 2 * np.pi * m[None, :] / Th * (pos - np.arange(S)[:, None] * Th / S)  # [S, M]
+        out.append((c * np.cos(ph)) @ state[:, h, 0] + (c * np.sin(ph)) @ state[:, h, 1])
+    return np.stack(out, axis=1)
+
+
+def two_parts(dtype, d, M, S, anchor, chunk=0):
     """A fresh sequence (the start mask hides slots of both sets) with a ragged last chunk, then its
     continuation past every threshold (the unmasked softmax)."""
     from test_gpu_parity import TOL, _bla, assert_close, gauss, to_dev
     bla = _bla()
-    print(f"slot folding: {dtype} d={d} M={M} S={S} anchor={anchor}", flush=True)
+    print(f"slot folding: {dtype} d={d} M={M} S={S} anchor={anchor} chunk={chunk}", flush=True)
     H, L = 2, 150
     T = [2.0 * M - 1.0, 2.3 * (2 * M - 1)]
     t0 = 0
@@ -82,18 +99,40 @@ def test_forward(dtype, d, M, S, anchor):
         q, k, v = gauss(100 * part + S, 1, H, L, d, dtype)
         q = q * 4.0  # scores of order one, so that every slot's weight differs
         o, nk, nv = bla.forward(*(to_dev(x, dtype) for x in (q, k, v)), T, M, S, t0=t0, state_k=sk, state_v=sv,
-                                phase_anchor=bool(anchor))
+                                phase_anchor=bool(anchor), chunk=chunk)
         torch.cuda.synchronize()
         sk64, sv64 = (None if x is None else x.double().cpu().numpy() for x in (sk, sv))
-        if anchor and part == 0:
-            ref = oracle.forward_anchored(q, k, v, T, M, S)[0]
-        elif anchor:
-            continue  # the anchored oracle keeps slot states, not mode states
+        if anchor:
+            slots = [None if x is None else anchored_slots(x, T, M, S, t0 - 1) for x in (sk64, sv64)]
+            ref = oracle.forward_anchored(q, k, v, T, M, S, t0=t0, slot_k=slots[0], slot_v=slots[1])[0]
         else:
             ref = oracle.forward(q, k, v, T, M, S, t0=t0, state_k=sk64, state_v=sv64)[0]
         assert_close(o.float().cpu().numpy(), ref, TOL[dtype], f"O part {part}")
         # far along the sequence: every threshold passed
         sk, sv, t0 = nk, nv, 4 * (2 * M - 1)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,d,M,S,anchor", CASES)
+def test_forward(dtype, d, M, S, anchor):
+    two_parts(dtype, d, M, S, anchor)
+
+
+CHUNK_CASES = [  # dtype, chunk, d, M, S, anchor: odd S, S below the padded count and equal to it
+    (torch.bfloat16, 16, 128, 64, 63, 1), (torch.bfloat16, 16, 64, 64, 127, 0), (torch.bfloat16, 16, 32, 64, 128, 1),
+    (torch.bfloat16, 16, 64, 32, 50, 1), (torch.bfloat16, 32, 32, 64, 64, 1), (torch.bfloat16, 32, 64, 32, 63, 0),
+    (torch.bfloat16, 32, 128, 64, 100, 1), (torch.bfloat16, 32, 128, 20, 33, 0), (torch.bfloat16, 32, 64, 64, 63, 1),
+    (torch.bfloat16, 128, 64, 64, 64, 1), (torch.bfloat16, 128, 32, 64, 127, 1), (torch.bfloat16, 128, 128, 32, 63, 0),
+    (torch.bfloat16, 128, 64, 32, 62, 1), (torch.float32, 16, 32, 64, 127, 0), (torch.float32, 16, 64, 64, 127, 1),
+    (torch.float32, 16, 128, 32, 64, 1), (torch.float32, 32, 32, 32, 63, 0), (torch.float32, 32, 64, 64, 128, 1),
+    (torch.float32, 128, 32, 20, 39, 1), (torch.float32, 128, 32, 32, 40, 0),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,chunk,d,M,S,anchor", CHUNK_CASES)
+def test_forward_chunks(dtype, chunk, d, M, S, anchor):
+    two_parts(dtype, d, M, S, anchor, chunk)
 
 
 BWD_CASES = [  # d, M, S: the slot edges, and every way the waves of a side share mode and head-dim tiles
