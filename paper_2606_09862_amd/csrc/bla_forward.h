@@ -142,7 +142,10 @@ template <typename T, int D, int MP, int SP, int CC = kChunk> struct Fwd : Geo<T
     // ... + the anchored twiddle row [2MP] of the chunk
     static constexpr size_t BASE_ELEMS = 2 * G::KT_ELEMS + (size_t)G::C * LDQU + (size_t)G::C * LDG +
                                          (size_t)D * G::LDZ + (size_t)2 * MP;
-    static constexpr size_t TAB_ELEMS = (size_t)ABROWS * LDAS + (size_t)2 * MP * LDAM + (size_t)G::C * LDE +
+    // the slot matrix's region is a multiple of 16 bytes (its folded rows are odd in number), so that
+    // the tables after it are as aligned as their 16-byte reads say
+    static constexpr size_t AB_ELEMS = ((size_t)ABROWS * LDAS + 7) / 8 * 8;
+    static constexpr size_t TAB_ELEMS = AB_ELEMS + (size_t)2 * MP * LDAM + (size_t)G::C * LDE +
                                         (size_t)2 * 2 * MP * LDR;
     // float32 rows rho and rho^C, then the int32 mask thresholds
     static constexpr size_t SMALL_BYTES = (size_t)3 * 2 * MP * 4 + (size_t)SP * 4;
@@ -164,6 +167,9 @@ template <typename T, int D, int MP, int SP, int CC = kChunk> struct Fwd : Geo<T
     static constexpr size_t TH_BYTES = FOLD && !TL ? (size_t)SP * 4 + (SPLIT ? (size_t)MP * sizeof(T) : 0) : 0;
     static constexpr size_t LDS_BYTES = TL ? FULL_BYTES : BASE_BYTES + (SPLIT ? SPLIT_BYTES : 0) + TH_BYTES;
     static_assert(SP % 32 == 0, "slot padding");
+    // start of the float32 rows and thresholds, which are read 16 bytes at a time
+    static_assert((TL ? FULL_BYTES - SMALL_BYTES : LDS_BYTES - TH_BYTES) % 16 == 0 && 2 * MP * 4 % 16 == 0,
+                  "16-byte reads of the rows and thresholds are aligned");
 };
 
 // The wave's fp32 state tiles: [owned mode tile][Re, Im][head-dim tile].
@@ -581,7 +587,7 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdA
     const T* fTw = (const T*)a.fTw + (size_t)h * C * 2 * MP;
     if constexpr (P::TL) {
         T* lABs = lPh + (size_t)2 * MP;
-        T* lABm = lABs + (size_t)P::ABROWS * P::LDAS;
+        T* lABm = lABs + P::AB_ELEMS;
         T* lEtab = lABm + (size_t)2 * MP * P::LDAM;
         T* lEbar = lEtab + (size_t)C * P::LDE;
         T* lErev = lEbar + (size_t)2 * MP * P::LDR;
