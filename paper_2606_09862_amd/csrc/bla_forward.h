@@ -73,13 +73,18 @@ template <typename T, int D, int MP, int CC = kChunk> struct Geo {
     // fragment over chunk tokens then carries zeros in reduction indices 16..31.
     static constexpr bool HALF = C % 32 != 0;
     static constexpr int OWN = (NMT + NW - 1) / NW;  // mode tiles owned per wave
-    // With fewer mode tiles than waves, NRM waves share a mode tile: wave w has tile w % NMT and is
-    // its part w / NMT.  They split its token tiles in phases A and B and its head-dim tiles of
+    // With fewer mode tiles than waves, NRM waves may share a mode tile: wave w has tile w % NMT and
+    // is its part w / NMT.  They split its token tiles in phases A and B and its head-dim tiles of
     // Z'_v in step (10); Z'_k, whose query products reduce over every head dim, each of them keeps
-    // whole.  (In float32, where a 16 x 16 x 32 product takes 256 cycles, the waves without a tile
-    // were the kernel's time: 32 sequences of 1000 tokens, d = 64, M = 32, 63 slots 71 -> 63 us;
-    // M = 16, 31 slots, 1500 tokens 80 -> 63.)
-    static constexpr int NRM = NMT < NW ? NW / NMT : 1;
+    // whole.  That pays in float32, where a 16 x 16 x 32 product takes 256 cycles, with two parts to a
+    // tile, and with four where the chunk has four token tiles or d is 128 (us of a call without /
+    // with, 256 sequences of 1024 tokens: 64-token chunks, d = 64, M = 16 236 / 180, M = 32, 63 slots
+    // 271 / 233; 32-token ones, d = 128, M = 16 459 / 427; 16-token ones, d = 64, M = 32 431 / 381).
+    // Elsewhere the copies of Z'_k cost more than the split saves (float32, d = 32, M = 16, 32-token
+    // chunks 132 / 140; bf16, 16-token chunks, d = 64, M = 32, 63 slots 153 / 173, d = 128, M = 16
+    // 176 / 256; 128-token chunks, d = 32, M = 64, 64 slots 270 / 284).
+    static constexpr int NRM =
+        sizeof(T) == 4 && NMT < NW && (NMT == 2 || C >= 64 || (C == 32 && D == 128)) ? NW / NMT : 1;
     static constexpr bool token_tile_of(int ct, int part)
     {
         // causal work grows with the token tile: 0, 3 | 1, 2 for two parts of four tiles
