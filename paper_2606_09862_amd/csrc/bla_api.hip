@@ -165,12 +165,17 @@ void make_plan_for(const bla_params* p, bool step, bool one_per_cu, Plan* pl)
     }
     if (!step && units > 0 && pl->nch > 1) {
         const int cus = device_cu_count();
-        // units that fill every CU once (the one-unit kernel: twice, where two workgroups share one;
-        // 128 sequences of 1024 tokens in 32-token chunks, d = 64, M = 32, 63 slots: 90 -> 73 us)
-        const int fill = pl->pair ? pl->upw : forward_wgs_per_cu(pl->bf16, pl->D, pl->MP, pl->SP, pl->C);
-        const long long target = (long long)cus * (one_per_cu ? 1 : fill);
+        // units that fill every CU once, or with two one-unit workgroups to a compute unit where that
+        // many fit
+        const int wgs = pl->pair || one_per_cu ? 1 : forward_wgs_per_cu(pl->bf16, pl->D, pl->MP, pl->SP, pl->C);
+        const long long target = (long long)cus * (one_per_cu ? 1 : pl->pair ? pl->upw : wgs > 1 ? 2 : 1);
         if (units < target) {
             long long want = (target + units - 1) / units;
+            // Several one-unit workgroups to a compute unit: no more segments than run in one round (us at
+            // d = 64, 1024 tokens; M = 32, 63 slots, 32-token chunks, uncut / two segments with two
+            // workgroups to a compute unit: 300 sequences 143 / 157, 400 142 / 194; M = 16, 16-token chunks,
+            // with three: 300 173 / 121, 400 171 / 237).
+            if (wgs > 1) want = units <= cus ? target / units : 2 * units <= (long long)cus * wgs ? 2 : 1;
             // A scan over the segments takes about 0.125 us each and a chunk of a segment 6.8 us
             // (d = M = 64): with few sequences, no more segments than balance the two
             // (4 sequences of 8192 tokens: 128 -> 64 segments,

@@ -171,6 +171,14 @@ template <typename T, int D, int MP, int SP, int CC = kChunk> struct Fwd : Geo<T
     // (and, for the split chain, the last row of A)
     static constexpr size_t TH_BYTES = FOLD && !TL ? (size_t)SP * 4 + (SPLIT ? (size_t)MP * sizeof(T) : 0) : 0;
     static constexpr size_t LDS_BYTES = TL ? FULL_BYTES : BASE_BYTES + (SPLIT ? SPLIT_BYTES : 0) + TH_BYTES;
+    // Workgroups of four waves that share a compute unit, each a wave per SIMD: as many as the LDS
+    // holds, and as the registers can (256 per lane for two, 168 for three; the kernel is bound to that
+    // number, which these shapes need no spills for, or up to seven registers at d = 128 in 32-token
+    // chunks).  Float32 at d = 128 needs 389 and more.
+    static constexpr int WGS =
+        G::NTHR != kThreads || (sizeof(T) == 4 && D == 128) || 2 * LDS_BYTES > kMaxLds ? 1
+        : MP <= 32 && D * (int)sizeof(T) <= 128 && 3 * LDS_BYTES <= kMaxLds            ? 3
+                                                                                       : 2;
     static_assert(SP % 32 == 0, "slot padding");
     // start of the float32 rows and thresholds, which are read 16 bytes at a time
     static_assert((TL ? FULL_BYTES - SMALL_BYTES : LDS_BYTES - TH_BYTES) % 16 == 0 && 2 * MP * 4 % 16 == 0,
@@ -530,7 +538,7 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void summary_kernel(FwdA
 // One workgroup per (b, h, segment): the chunk loop over the segment.  AN: anchored slots
 // (a separate instantiation, so that the rotating form keeps its own register allocation).
 template <typename T, int D, int MP, int SP, bool AN, int CC = kChunk>
-__global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR)) void forward_kernel(FwdArgs a)
+__global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR), (Fwd<T, D, MP, SP, CC>::WGS)) void forward_kernel(FwdArgs a)
 {
     using P = Fwd<T, D, MP, SP, CC>;
     using GG = Geo<T, D, MP, CC>;

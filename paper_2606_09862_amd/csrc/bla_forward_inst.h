@@ -66,15 +66,13 @@ hipError_t launch_one_summary(const Plan& p, const FwdArgs& a, hipStream_t s)
     }
 }
 
-// Workgroups of the one-unit forward kernel that share a compute unit: two where their LDS fits
-// twice (their four waves each then fill two waves per SIMD).
+// Workgroups of the one-unit forward kernel that share a compute unit.
 template <typename T, int D, int MP, int SP> int one_unit_wgs(int C)
 {
-    auto two = [](size_t b) { return 2 * b <= kMaxLds ? 2 : 1; };
     switch (C) {
-    case 16: return two(Fwd<T, D, MP, SP, 16>::LDS_BYTES);
-    case 32: return two(Fwd<T, D, MP, SP, 32>::LDS_BYTES);
-    case 64: return two(Fwd<T, D, MP, SP, 64>::LDS_BYTES);
+    case 16: return Fwd<T, D, MP, SP, 16>::WGS;
+    case 32: return Fwd<T, D, MP, SP, 32>::WGS;
+    case 64: return Fwd<T, D, MP, SP, 64>::WGS;
     }
     return 1;
 }

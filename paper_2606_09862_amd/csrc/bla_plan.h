@@ -325,7 +325,7 @@ bool tables_overwritten(const void* ws, size_t n);
 // Sequence units per workgroup of the bf16 pair kernel (0: the one-unit forward kernel runs).
 int forward_units_per_wg(int bf16, int D, int MP, int SP);
 
-// Workgroups of the one-unit forward kernel that share a compute unit (1 or 2).
+// Workgroups of the one-unit forward kernel that share a compute unit (1 to 3).
 int forward_wgs_per_cu(int bf16, int D, int MP, int SP, int C);
 
 }  // namespace bla

@@ -47,3 +47,21 @@ def test_records_of_tables_end_where_another_call_writes():
     script += [("keep 0 10000 5 0", 0), ("keep 0 10690 5 69", 1)]
     got = run("records", [x for x, _ in script])
     assert [int(x) for x in got] == [y for _, y in script if y is not None]
+
+
+def test_segments_of_the_one_unit_kernels_run_in_one_round():
+    """256 compute units (the host's default).  With two or three workgroups to a compute unit the
+    segments fill two, and never start a second round; whether so many fit is a matter of
+    registers as well as of LDS (float32 at d = 128 takes the register file for one)."""
+    def nseg(units, d, M, S, bf16, chunk, anchor=0):
+        return plans([("f", 1, units, 1024, d, M, S, bf16, chunk, anchor)])[0]["nseg"]
+
+    for anchor in (0, 1):
+        assert [nseg(u, 128, 16, 31, 0, 16, anchor) for u in (100, 128, 200, 256, 400)] == [3, 2, 2, 1, 1]
+        assert [nseg(u, 128, 16, 31, 1, 32, anchor) for u in (100, 128, 200, 256, 400)] == [5, 4, 2, 2, 1]
+    assert [nseg(u, 64, 16, 31, 1, 16) for u in (128, 200, 256, 300, 384, 385, 511)] == [4, 2, 2, 2, 2, 1, 1]
+    cases = [("f", 1, u, 2000, d, M, S, bf16, chunk, 0) for u in (5, 100, 171, 255, 257, 300, 390, 511) for d in (32, 64, 128)
+             for M, S in ((16, 31), (32, 63), (64, 64), (64, 127)) for bf16 in (0, 1) for chunk in (16, 32, 64, 128)]
+    for c, p in zip(cases, plans(cases)):
+        if p is not None and not p["pair"] and p["nseg"] > 1 and c[2] > 256:
+            assert c[2] * p["nseg"] <= 768, (c, p["nseg"])
