@@ -419,7 +419,7 @@ __global__ __launch_bounds__((Bwd16<D, MP, SP>::NTHR)) void bwd16_kernel(BwdArgs
     }
     copy_conj_phase<MP, NTHR>(sE, LE, (const bf16*)a.Etab + (size_t)h * C * 2 * MP, tid);
     copy_table<bf16, P::ABROWS, 2 * MP, LE, NTHR>(sAB, (const bf16*)a.ABs, tid);
-    for (int i = tid; i < SP; i += NTHR) sTheta[i] = slot_threshold<SP>(a.theta + (size_t)h * SP, i, a.S);
+    for (int i = tid; i < SP; i += NTHR) sTheta[i] = slot_threshold<P::FOLD>(a.theta + (size_t)h * SP, i, a.S, SP);
     load_rho_rows<NTHR>(sRhoC, E32h, a, MP, tid);
     const bool last_row = P::FOLD && a.S == SP;  // slot S/2 in row 0 of the mirror set
 

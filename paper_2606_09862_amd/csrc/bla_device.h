@@ -351,7 +351,8 @@ __device__ __forceinline__ void twiddle_h(halfx4 c, halfx4 n, floatx4& re, float
 // 126 -> 124; 64 of 2048 at d = 128, M = 64, 127 slots 284 -> 103 (the tiles now fit the pair
 // kernel); 16 of 65536 at d = M = 128 slots 1094 -> 1057; 32 of 1000 in float32, M = 32, 63
 // slots 79 -> 72.  Where the padded slot count SP is 32, its one 32-slot reduction block would be
-// half empty and nothing is saved; from 64 on the kernels keep the SP/2 = HP rows s < HP and hold every token's slots as two sets of HP/16
+// half empty and nothing is saved; from 64 on the kernels (the one-unit forward kernels with 64 not
+// everywhere, see Fwd::FOLD) keep the SP/2 = HP rows s < HP and hold every token's slots as two sets of HP/16
 // accumulator tiles: main (slot s of row s) and mirror (slot S - s of row s).  Row 0 has no
 // partner.  When S == SP, slot S/2 would be row HP: its matrix row is A[HP] alone (B is zero
 // there), and since B[0] is zero too, it takes row 0's place in the second set: q_0 is its score
@@ -371,9 +372,9 @@ __host__ __device__ inline int folded_slot(int i, int S, int SP)
 
 // Start-mask threshold of entry i of the kernels' slot order (folded or natural), from the
 // head's natural thresholds; INT32_MAX for an entry without a slot.
-template <int SP> __device__ __forceinline__ int slot_threshold(const int* theta, int i, int S)
+template <bool FOLD> __device__ __forceinline__ int slot_threshold(const int* theta, int i, int S, int SP)
 {
-    if constexpr (slots_folded(SP)) {
+    if constexpr (FOLD) {
         const int s = folded_slot(i, S, SP);
         return s < 0 ? INT32_MAX : theta[s];
     } else {

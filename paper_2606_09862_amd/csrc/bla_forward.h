@@ -130,16 +130,9 @@ template <typename T, int D, int MP, int SP, int CC = kChunk> struct Fwd : Geo<T
     using G = Geo<T, D, MP, CC>;
     static constexpr int NST = SP / 16;
     static constexpr int KBS = SP / 32;
-    // Slot rows of the tables that the kernel reads (bla_device.h, slot folding), their tiles
-    // and reduction blocks; folded tables also hold the last row, as row HP of ABs and column
-    // HP of ABm (in the row padding).
-    static constexpr bool FOLD = slots_folded(SP);
-    static constexpr int HP = slot_rows(SP), NHT = HP / 16, KBH = HP / 32;
-    static constexpr int ABROWS = FOLD ? HP + 1 : SP, ABCOLS = FOLD ? HP + G::PAD : SP;
     static constexpr int LDG = G::C + G::PAD;    // GT:   [C tokens][LDG]
     static constexpr int LDU = 2 * MP + G::PAD;  // UT:   [C tokens][LDU]
     static constexpr int LDAS = 2 * MP + G::PAD; // ABs:  [ABROWS][LDAS]
-    static constexpr int LDAM = HP + G::PAD;     // ABm:  [2MP][LDAM]
     static constexpr int LDE = 2 * MP + G::PAD;  // Etab: [C][LDE]  (also the phase twiddles)
     static constexpr int LDR = G::C + G::PAD;    // EbarT, ErevT: [2MP][LDR]
     // Qs (read in phase A) and UT (written after the next barrier) share one buffer.
@@ -147,15 +140,34 @@ template <typename T, int D, int MP, int SP, int CC = kChunk> struct Fwd : Geo<T
     // ... + the anchored twiddle row [2MP] of the chunk
     static constexpr size_t BASE_ELEMS = 2 * G::KT_ELEMS + (size_t)G::C * LDQU + (size_t)G::C * LDG +
                                          (size_t)D * G::LDZ + (size_t)2 * MP;
-    // the slot matrix's region is a multiple of 16 bytes (its folded rows are odd in number), so that
-    // the tables after it are as aligned as their 16-byte reads say
-    static constexpr size_t AB_ELEMS = ((size_t)ABROWS * LDAS + 7) / 8 * 8;
-    static constexpr size_t TAB_ELEMS = AB_ELEMS + (size_t)2 * MP * LDAM + (size_t)G::C * LDE +
-                                        (size_t)2 * 2 * MP * LDR;
+    static constexpr size_t BASE_BYTES = BASE_ELEMS * sizeof(T);
     // float32 rows rho and rho^C, then the int32 mask thresholds
     static constexpr size_t SMALL_BYTES = (size_t)3 * 2 * MP * 4 + (size_t)SP * 4;
-    static constexpr size_t BASE_BYTES = BASE_ELEMS * sizeof(T);
-    static constexpr size_t FULL_BYTES = BASE_BYTES + TAB_ELEMS * sizeof(T) + SMALL_BYTES;
+    // Elements of the slot matrix's region for `rows` rows: a multiple of 16 bytes (folded rows are
+    // odd in number), so that the tables after it are as aligned as their 16-byte reads say; and
+    // the LDS with every table, for slot matrices of `rows` rows and hp columns.
+    static constexpr size_t ab_elems(int rows) { return ((size_t)rows * LDAS + 7) / 8 * 8; }
+    static constexpr size_t full_bytes(int rows, int hp)
+    {
+        return BASE_BYTES + SMALL_BYTES +
+               (ab_elems(rows) + (size_t)2 * MP * (hp + G::PAD) + (size_t)G::C * LDE + (size_t)2 * 2 * MP * LDR) * sizeof(T);
+    }
+    static constexpr int per_cu(size_t bytes) { return 2 * bytes <= kMaxLds ? 2 : 1; }
+    // Slot rows of the tables that the kernel reads (bla_device.h, slot folding), their tiles
+    // and reduction blocks; folded tables also hold the last row, as row HP of ABs and column
+    // HP of ABm (in the row padding).  In bf16 with 64 padded slots, where the folded sums cost as
+    // much as the products that they save, the slots are folded where that brings the tables into LDS
+    // or a second workgroup onto the compute unit, and at d = 128 (us of a call without / with,
+    // 512 sequences of 512 tokens, 32-token chunks: d = 64, M = 64 144 / 152, M = 32 77 / 80; but
+    // d = 32, M = 64 122 / 78; d = 128, M = 64 236 / 231).
+    static constexpr bool FOLD =
+        slots_folded(SP) && !(sizeof(T) == 2 && SP == 64 && D <= 64 && full_bytes(SP, SP) <= kMaxLds &&
+                              per_cu(full_bytes(SP, SP)) == per_cu(full_bytes(SP / 2 + 1, SP / 2)));
+    static constexpr int HP = FOLD ? slot_rows(SP) : SP, NHT = HP / 16, KBH = HP / 32;
+    static constexpr int ABROWS = FOLD ? HP + 1 : SP, ABCOLS = FOLD ? HP + G::PAD : SP;
+    static constexpr int LDAM = HP + G::PAD;     // ABm:  [2MP][LDAM]
+    static constexpr size_t AB_ELEMS = ab_elems(ABROWS);
+    static constexpr size_t FULL_BYTES = full_bytes(ABROWS, HP);
     static constexpr bool TL = FULL_BYTES <= kMaxLds;  // tables live in LDS
     // Split chain (bf16, eight waves, four token tiles, tables outside LDS): steps (4)-(9) are
     // split by output columns -- each wave forms one slot tile of the scores, one mode tile of
@@ -614,7 +626,7 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR), (Fwd<T, D, MP, SP, CC>::
         copy_table<float, 1, 2 * MP, 2 * MP, GG::NTHR>(lRho, E32h + 2 * MP, tid);                    // rho
         copy_table<float, 1, 2 * MP, 2 * MP, GG::NTHR>(lRho + 2 * MP, E32h + (size_t)C * 2 * MP, tid);  // rho^C
         copy_table<float, 1, 2 * MP, 2 * MP, GG::NTHR>(lRho + 4 * MP, E32h + (size_t)c_last * 2 * MP, tid);  // rho^c_last
-        for (int i = tid; i < SP; i += GG::NTHR) lTheta[i] = slot_threshold<SP>(thh, i, a.S);
+        for (int i = tid; i < SP; i += GG::NTHR) lTheta[i] = slot_threshold<P::FOLD>(thh, i, a.S, SP);
         tABs = lABs;
         tABm = lABm;
         tEtab = lEtab;
@@ -635,7 +647,7 @@ __global__ __launch_bounds__((Geo<T, D, MP, CC>::NTHR), (Fwd<T, D, MP, SP, CC>::
         rhoL = E32h + (size_t)c_last * 2 * MP;
         if constexpr (P::FOLD) {
             int* lTheta = reinterpret_cast<int*>(lds_raw + P::LDS_BYTES - P::TH_BYTES);
-            for (int i = tid; i < SP; i += GG::NTHR) lTheta[i] = slot_threshold<SP>(thh, i, a.S);
+            for (int i = tid; i < SP; i += GG::NTHR) lTheta[i] = slot_threshold<P::FOLD>(thh, i, a.S, SP);
             if constexpr (P::SPLIT) {
                 T* lLast = reinterpret_cast<T*>(lTheta + SP);
                 for (int i = tid; i < MP; i += GG::NTHR) lLast[i] = tABs[(size_t)P::HP * 2 * MP + i];

@@ -770,7 +770,7 @@ __global__ __launch_bounds__((256 * Pair<D, MP, SP>::U)) void forward_pair_kerne
         sRho[2 * MP + i] = E32h[(size_t)C * 2 * MP + i];
         sRho[4 * MP + i] = E32h[(size_t)c_last * 2 * MP + i];
     }
-    for (int i = tid; i < SP; i += 256 * P::U) sTheta[i] = slot_threshold<SP>(a.theta + (size_t)h * SP, i, a.S);
+    for (int i = tid; i < SP; i += 256 * P::U) sTheta[i] = slot_threshold<P::FOLD>(a.theta + (size_t)h * SP, i, a.S, SP);
     const bool last_row = P::FOLD && a.S == SP;  // slot S/2 in row 0 of the mirror set
 
     const int ch0 = seg * a.cps;
