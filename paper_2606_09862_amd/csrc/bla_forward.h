@@ -168,7 +168,10 @@ template <typename T, int D, int MP, int SP, int CC = kChunk> struct Fwd : Geo<T
     static constexpr int LDAM = HP + G::PAD;     // ABm:  [2MP][LDAM]
     static constexpr size_t AB_ELEMS = ab_elems(ABROWS);
     static constexpr size_t FULL_BYTES = full_bytes(ABROWS, HP);
-    static constexpr bool TL = FULL_BYTES <= kMaxLds;  // tables live in LDS
+    // Tables live in LDS, where they fit.  Not in float32 for 128 padded slots in 16-token chunks at 64
+    // modes: they would take the second workgroup's place (d = 64, 512 sequences of 512 tokens 754
+    // without, 827 with).
+    static constexpr bool TL = FULL_BYTES <= kMaxLds && !(sizeof(T) == 4 && MP == 64 && SP == 128 && CC == 16);
     // Split chain (bf16, eight waves, four token tiles, tables outside LDS): steps (4)-(9) are
     // split by output columns -- each wave forms one slot tile of the scores, one mode tile of
     // the readout weights and one head-dim tile of the output, for every token of the chunk,
