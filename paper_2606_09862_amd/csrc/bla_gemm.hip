@@ -106,15 +106,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BT == 128 ?
     }
 }
 
-// The sizes that this kernel takes from the vendor library: a reduction of at most 512, or a small
-// product.  Measured on whole layers (us of a call, host or device whichever is longer; library / this
-// kernel): 64 tokens of width 64 54 / 22, 100 of 256 59 / 28, 700 of 96 57 / 26, 32768 of 256
-// 79.5 / 76, 16384 of 512 101 / 99, 2000 of 1024 73 / 75; past it the library is faster, 8192 of 1024
-// 138 / 149, 4096 of 2048 209 / 243.  Its calls take 65-100 us on the host, this kernel's 3.
+// The sizes that this kernel takes from the vendor library: a reduction of at most 512, or one of at
+// most 1024 in a small product.  Measured on whole layers (us of a call among others; library / this
+// kernel): 64 tokens of width 64 38 / 12, 500 of 256 43 / 22, 16000 of 256 63 / 50, 16000 of 512
+// 86 / 86, 4000 of 640 59 / 51, 1000 of 1024 43 / 42, with the output product alone 4000 of 1024
+// 67 / 69.  A workgroup walks its reduction alone, so longer ones leave the chip idle where the library
+// splits them (16 tokens of width 1536 38 / 55, 200 of 2048 59 / 88).  A layer through the library
+// takes 37 us of host time at the least, this kernel's launch 3.
 bool gemm_takes(long long m, long long n, long long k)
 {
     if (m <= 0 || n <= 0 || k <= 0 || n % 8 || k % 8 || n > INT32_MAX || k > INT32_MAX) return false;
-    return k <= 512 || (double)m * (double)n * (double)k <= 6e9;
+    const double ops = (double)m * (double)n * (double)k;
+    return k <= 512 || (k <= 768 && ops <= 6e9) || (k <= 1024 && ops <= 3.2e9);
 }
 
 hipError_t launch_gemm(const bf16* X, const bf16* W, bf16* Y, long long m, int n, int k, hipStream_t s)

@@ -82,8 +82,17 @@ static int slots()
     return 0;
 }
 
+// products: reads lines "m n k"; prints whether the library's own kernel forms that product.
+static int products()
+{
+    long long m, n, k;
+    while (scanf("%lld %lld %lld", &m, &n, &k) == 3) printf("%d\n", gemm_takes(m, n, k));
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
+    if (argc == 2 && !strcmp(argv[1], "products")) return products();
     if (argc == 2 && !strcmp(argv[1], "slots")) return slots();
     if (argc == 2 && !strcmp(argv[1], "records")) return records();
     if (argc == 2 && !strcmp(argv[1], "plan")) return plans();

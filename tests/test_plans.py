@@ -1,5 +1,5 @@
-"""The launch plans, on the host: where the tables and the scratch lie in a workspace, and the record of
-the tables that calls left in workspaces."""
+"""The launch plans, on the host: where the tables and the scratch lie in a workspace, the record of the
+tables that calls left in workspaces, and which products of a layer the library forms itself."""
 import random
 
 from host_probe import plans, run
@@ -65,3 +65,12 @@ def test_segments_of_the_one_unit_kernels_run_in_one_round():
     for c, p in zip(cases, plans(cases)):
         if p is not None and not p["pair"] and p["nseg"] > 1 and c[2] > 256:
             assert c[2] * p["nseg"] <= 768, (c, p["nseg"])
+
+
+def test_products_with_long_reductions_go_to_the_vendor_library():
+    """The own kernel does not split a reduction, so past 1024 it loses at any number of tokens."""
+    takes = lambda m, n, k: run("products", [f"{m} {n} {k}"]) == ["1"]
+    assert takes(1, 96, 32) and takes(10 ** 6, 1536, 512) and takes(4000, 1920, 640) and takes(1000, 3072, 1024)
+    for m in (1, 16, 200, 500, 4000):
+        assert not takes(m, 3 * 1536, 1536) and not takes(m, 2048, 2048)
+    assert not takes(4000, 1024, 1024) and not takes(8000, 2304, 768) and not takes(8, 12, 64) and not takes(0, 96, 32)
