@@ -414,9 +414,11 @@ __attribute__((amdgpu_waves_per_eu(SumPair<D, MP>::MINB * SumPair<D, MP>::NW / 4
     // Workgroups are dealt to the eight XCDs by linear index (x mod 8 with a row length that
     // is a multiple of 8); the DS slices of a block take indices 8 apart, so they share an
     // XCD and its L2 and each 128-byte line of K and V is fetched from HBM once.
-    const int xq = blockIdx.x / 8, ds = xq % DS, job = (xq / DS) * 8 + blockIdx.x % 8;
+    // The eight jobs of such a group are dealt from another XCD on for each head, so that few jobs a head
+    // (many heads of one sequence) do not all land on the first.
+    const int h = blockIdx.y, xq = blockIdx.x / 8, ds = xq % DS, job = (xq / DS) * 8 + (blockIdx.x + h) % 8;
     if (job >= a.B * a.nbs) return;  // grid padding (whole workgroup, before any barrier)
-    const int h = blockIdx.y, blk = job % a.nbs, b = job / a.nbs;
+    const int blk = job % a.nbs, b = job / a.nbs;
     const int bh = b * a.H + h;
     const size_t first = (size_t)blk * a.cpb * C;
     const int ts = a.in_t;
