@@ -39,10 +39,27 @@ template <typename T, int D, int MP, int SP, int CC = kChunk> constexpr bool fit
 // M <= 64 (padded modes up to 64), where their tiles and registers fit.
 template <int MP, int CC> constexpr bool chunk_built() { return CC == kChunk || MP <= 64; }
 
+// Units per workgroup of the bf16 pair kernel for a shape (0: the shape uses forward_kernel).
+template <typename T, int D, int MP, int SP> constexpr int pair_units()
+{
+    if constexpr (sizeof(T) == 2) {
+        return Pair<D, MP, SP>::FITS ? Pair<D, MP, SP>::U : 0;
+    } else {
+        return 0;
+    }
+}
+
+// Whether the one-unit forward kernel is built for a shape and chunk length: the pair kernel takes
+// every call of 64-token chunks that it exists for.
+template <typename T, int D, int MP, int SP, int CC> constexpr bool one_unit_built()
+{
+    return chunk_built<MP, CC>() && fits<T, D, MP, SP, CC>() && !(CC == kChunk && pair_units<T, D, MP, SP>() > 0);
+}
+
 template <typename T, int D, int MP, int SP, int CC>
 hipError_t launch_one_unit(const Plan& p, const FwdArgs& a, hipStream_t s)
 {
-    if constexpr (chunk_built<MP, CC>() && fits<T, D, MP, SP, CC>()) {
+    if constexpr (one_unit_built<T, D, MP, SP, CC>()) {
         const dim3 grid((unsigned)(p.B * p.H * p.nseg));
         if (a.anchor)
             hipLaunchKernelGGL((forward_kernel<T, D, MP, SP, true, CC>), grid, dim3(Geo<T, D, MP, CC>::NTHR), 0, s, a);
@@ -57,7 +74,8 @@ hipError_t launch_one_unit(const Plan& p, const FwdArgs& a, hipStream_t s)
 template <typename T, int D, int MP, int CC>
 hipError_t launch_one_summary(const Plan& p, const FwdArgs& a, hipStream_t s)
 {
-    if constexpr (chunk_built<MP, CC>()) {
+    // bf16 64-token chunks are summarised by summary_pair_kernel
+    if constexpr (chunk_built<MP, CC>() && !(sizeof(T) == 2 && CC == kChunk)) {
         hipLaunchKernelGGL((summary_kernel<T, D, MP, CC>), dim3((unsigned)(p.B * p.H * p.nbs)),
                            dim3(Geo<T, D, MP, CC>::NTHR), 0, s, a);
         return hipGetLastError();
@@ -77,14 +95,13 @@ template <typename T, int D, int MP, int SP> int one_unit_wgs(int C)
     return 1;
 }
 
-// Whether the one-unit forward kernel exists for a shape and chunk length.
 template <typename T, int D, int MP, int SP> bool one_unit_fits(int C)
 {
     switch (C) {
-    case 16: return chunk_built<MP, 16>() && fits<T, D, MP, SP, 16>();
-    case 32: return chunk_built<MP, 32>() && fits<T, D, MP, SP, 32>();
-    case 64: return fits<T, D, MP, SP, 64>();
-    case 128: return chunk_built<MP, 128>() && fits<T, D, MP, SP, 128>();
+    case 16: return one_unit_built<T, D, MP, SP, 16>();
+    case 32: return one_unit_built<T, D, MP, SP, 32>();
+    case 64: return one_unit_built<T, D, MP, SP, 64>();
+    case 128: return one_unit_built<T, D, MP, SP, 128>();
     }
     return false;
 }
@@ -93,16 +110,6 @@ template <typename T, int D, int MP, int SP> struct Launch {
     static hipError_t forward(const Plan& p, const FwdArgs& a, hipStream_t s);
     static hipError_t summary(const Plan& p, const FwdArgs& a, hipStream_t s);
 };
-
-// Units per workgroup of the bf16 pair kernel for a shape (0: the shape uses forward_kernel).
-template <typename T, int D, int MP, int SP> constexpr int pair_units()
-{
-    if constexpr (sizeof(T) == 2) {
-        return Pair<D, MP, SP>::FITS ? Pair<D, MP, SP>::U : 0;
-    } else {
-        return 0;
-    }
-}
 
 }  // namespace bla
 
@@ -148,7 +155,7 @@ template <typename T, int D, int MP, int SP> constexpr int pair_units()
                 return hipGetLastError();                                                               \
             }                                                                                           \
         }                                                                                               \
-        if constexpr (sizeof(T) == 2) {                                                                 \
+        if constexpr (sizeof(T) == 2 && pair_units<T, D, MP, SP>() == 0) {                              \
             if (p.C == kChunk) { /* bf16, 64-token chunks: the sliced summary kernel */                 \
                 hipLaunchKernelGGL((summary_pair_kernel<D, MP, true>),                                  \
                                    dim3((unsigned)summary_grid_x<D, MP>((long long)p.B * p.nbs), (unsigned)p.H),  \
