@@ -49,8 +49,9 @@ METRIC = "BLA forward tokens/sec at L=4096 (1 MI355X) + % of MFMA/HBM roofline"
 
 def forward_flops_per_token_head(C, d, M, S):
     """Algorithmic flops of the chunked form per (token, head); the C x C terms count their
-    causal half with the diagonal: 2(C+1)d + 4(C+1)M + 8MS + 16Md."""
-    return 2 * (C + 1) * d + 4 * (C + 1) * M + 8 * M * S + 16 * M * d
+    causal half with the diagonal: 2(C+1)d + 4(C+1)M + 8M(S/2 + 1) + 16Md.  Slots s and S - s
+    share a row of the slot matrices, so scores and readout weights meet S/2 + 1 rows, not S."""
+    return 2 * (C + 1) * d + 4 * (C + 1) * M + 8 * M * (S // 2 + 1) + 16 * M * d
 
 
 def decay_flops_per_token_head(d, S, sub=16):
@@ -64,10 +65,10 @@ def decay_flops_per_token_head(d, S, sub=16):
 def backward_flops_per_token_head(C, d, M, S):
     """Algorithmic flops of the backward's reverse walk per (token, head), causal halves of the
     C x C terms with the diagonal: the Gram tiles Q K^T, dO V^T and the tril(H) products for dq,
-    dk, dv (5(C+1)d); G conj(E), Gd conj(E), H_q, H_v (8(C+1)M); scores, dP, W'' and Wq''
-    (16MS); Q Z'_k^T, dO Z'_v^T, Re(Wq'' Z'_k), the two adjoint terms of dk and dv, the state
-    rebuilt by subtraction and the adjoint update (36Md)."""
-    return 5 * (C + 1) * d + 8 * (C + 1) * M + 16 * M * S + 36 * M * d
+    dk, dv (5(C+1)d); G conj(E), Gd conj(E), H_q, H_v (8(C+1)M); scores, dP, W'' and Wq'' on
+    the S/2 + 1 slot rows (16M(S/2 + 1)); Q Z'_k^T, dO Z'_v^T, Re(Wq'' Z'_k), the two adjoint
+    terms of dk and dv, the state rebuilt by subtraction and the adjoint update (36Md)."""
+    return 5 * (C + 1) * d + 8 * (C + 1) * M + 16 * M * (S // 2 + 1) + 36 * M * d
 
 
 def forward_bytes(B, H, L, d, M, io_bytes):
