@@ -106,18 +106,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BT == 128 ?
     }
 }
 
-// The sizes that this kernel takes from the vendor library: a reduction of at most 512, or one of at
-// most 1024 in a small product.  Measured on whole layers (us of a call among others; library / this
-// kernel): 64 tokens of width 64 38 / 12, 500 of 256 43 / 22, 16000 of 256 63 / 50, 16000 of 512
-// 86 / 86, 4000 of 640 59 / 51, 1000 of 1024 43 / 42, with the output product alone 4000 of 1024
-// 67 / 69.  A workgroup walks its reduction alone, so longer ones leave the chip idle where the library
-// splits them (16 tokens of width 1536 38 / 55, 200 of 2048 59 / 88).  A layer through the library
-// takes 37 us of host time at the least, this kernel's launch 3.
+// The sizes that this kernel takes from the vendor library.  A workgroup walks its reduction alone, so a long
+// one leaves the chip idle where the library splits it (a layer of 16 tokens of width 1536: library 38 us /
+// this kernel 55, 200 of 2048 59 / 88); and for large products of widths that are multiples of 256, or past
+// 512, the library has kernels that are faster once the device, not its 18 us of host time, is what a
+// product takes (one product: 32768 tokens of width 512 to 1536 columns 62 / 71, 8192 22 / 22; 65536 of
+// width 256 to 768 columns 42 / 47, 32768 29 / 27; 8528 of 640 to 640 17 / 22, but a whole layer of 4000
+// of 640 59 / 51, of 1000 of 1024 43 / 42).  Widths between those it has none for: 65536 of 384 to 1152 118 / 86,
+// 131072 of 448 to 448 108 / 83.  Both products of a layer go the same way (n does not matter).
 bool gemm_takes(long long m, long long n, long long k)
 {
     if (m <= 0 || n <= 0 || k <= 0 || n % 8 || k % 8 || n > INT32_MAX || k > INT32_MAX) return false;
-    const double ops = (double)m * (double)n * (double)k;
-    return k <= 512 || (k <= 768 && ops <= 6e9) || (k <= 1024 && ops <= 3.2e9);
+    if (k < 512 && k % 256) return true;
+    return (double)m * (double)k * (double)k <= (k <= 768 ? 2.2e9 : k <= 1024 ? 1.1e9 : 0.0);
 }
 
 hipError_t launch_gemm(const bf16* X, const bf16* W, bf16* Y, long long m, int n, int k, hipStream_t s)

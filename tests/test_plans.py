@@ -67,10 +67,13 @@ def test_segments_of_the_one_unit_kernels_run_in_one_round():
             assert c[2] * p["nseg"] <= 768, (c, p["nseg"])
 
 
-def test_products_with_long_reductions_go_to_the_vendor_library():
-    """The own kernel does not split a reduction, so past 1024 it loses at any number of tokens."""
+def test_products_that_the_vendor_library_takes():
+    """The own kernel does not split a reduction, so past 1024 it loses at any number of tokens, and widths of 256
+    and 512 go back to the library once many tokens hide its start."""
     takes = lambda m, n, k: run("products", [f"{m} {n} {k}"]) == ["1"]
-    assert takes(1, 96, 32) and takes(10 ** 6, 1536, 512) and takes(4000, 1920, 640) and takes(1000, 3072, 1024)
+    assert takes(1, 96, 32) and takes(10 ** 6, 1152, 384) and takes(4000, 1920, 640) and takes(1000, 3072, 1024)
+    assert takes(32768, 768, 256) and takes(8192, 512, 512) and not takes(65536, 256, 256)
+    assert not takes(16384, 1536, 512) and not takes(8528, 640, 640)
     for m in (1, 16, 200, 500, 4000):
         assert not takes(m, 3 * 1536, 1536) and not takes(m, 2048, 2048)
     assert not takes(4000, 1024, 1024) and not takes(8000, 2304, 768) and not takes(8, 12, 64) and not takes(0, 96, 32)
