@@ -291,7 +291,8 @@ bla_status bla_backward_timed(const bla_params* p, const double* T, const void* 
  * with x, y [B, L, D] row-major, W_qkv [D, 3D] (columns h d_k .. h d_k + d_k - 1 of block 0,
  * 1, 2 are head h's query, key and value projections), W_o [D, D] (row h d_k + e takes element
  * e of head h's output), all bf16; the products accumulate in float32 (the library's own kernel
- * for D <= 512 and small products, hipBLASLt for large ones) and q, k, v and o are rounded to bf16 between the steps.  p describes the operator (p->d_k = p->d_v is
+ * for small products and for widths below 512 that are not multiples of 256, hipBLASLt for the others) and q, k, v
+ * and o are rounded to bf16 between the steps.  p describes the operator (p->d_k = p->d_v is
  * the head width, p->L the tokens); states as for bla_forward.  The operator reads q, k, v in
  * place from the projection output [B, L, 3, H, d_k] and writes o in place as [B, L, H, d_k],
  * the output projection's input.  The workspace holds those two tensors, the operator's

@@ -179,7 +179,9 @@ void make_plan_for(const bla_params* p, bool step, bool one_per_cu, Plan* pl)
             // A scan over the segments takes about 0.125 us each and a chunk of a segment 6.8 us
             // (d = M = 64): with few sequences, no more segments than balance the two
             // (4 sequences of 8192 tokens: 128 -> 64 segments,
-            // 58 -> 48 us; one of 16384: 256 -> 86, 74 -> 48 us).
+            // 58 -> 48 us; one of 16384: 256 -> 86, 74 -> 48 us).  Chunks of other shapes take less or more, so
+            // theirs is off the balance by the root of that (still 323 -> 57 us for 6 sequences of 18910 tokens
+            // at d = 32, M = 48, 95 slots against the one-unit kernels).
             if (pl->pair && pl->nch > kMaxPassChunks) {
                 const long long most = (long long)sqrt(54.0 * pl->nch);
                 if (want > most) want = most;

@@ -1,7 +1,7 @@
 // Table construction, the scan over block summaries, and state copies.
 //
-// Tables are built on the device in double precision (library sincos) from the
-// exact integer phase m*j mod T, then rounded once to float32 / the operand type.
+// Tables are built on the device in double precision (library sincospi of the phase's
+// revolutions m j / T reduced to [0, 1)), then rounded once to float32 / the operand type.
 #include <math.h>
 #include <stdint.h>
 

@@ -1,5 +1,5 @@
 // Row-major bf16 product Y [m, n] = X [m, k] W [k, n] with float32 accumulation: the projections of
-// a layer whose model width is small.
+// a layer (the sizes: gemm_takes).
 //
 // A workgroup of four waves forms a BT x BT tile of Y, each wave a quarter (WT x WT); the reduction
 // runs in blocks of 64 staged through LDS, the next block loaded into registers meanwhile.  The

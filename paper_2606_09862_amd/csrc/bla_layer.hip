@@ -8,8 +8,8 @@
 //                        written in place as [B, L, H, d] (the operator's strided form)
 //   y = o W_o            W_o [D, D]
 //
-// The two products are plain dense GEMMs: small widths run gemm_kernel, large ones the vendor
-// library (gemm_takes); the operator
+// The two products are plain dense GEMMs: small ones run gemm_kernel, large ones of widths that the
+// vendor library has faster kernels for run there (gemm_takes); the operator
 // runs in this library's kernels and reads and writes the GEMMs' row-major tensors
 // directly, so no head split or merge pass touches memory.
 #include <stdint.h>
