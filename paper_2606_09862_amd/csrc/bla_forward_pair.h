@@ -57,8 +57,10 @@ template <int D, int MP, int SP> struct Pair {
     static constexpr int KBD = D / 32, KBM = 2 * MP / 32, KBC = C / 32, KBS = SP / 32;
     static constexpr int OWN = (NMT + WPU - 1) / WPU;
     // With two mode tiles, waves 0, 1 own Z'_k and waves 2, 3 Z'_v of tiles 0, 1; otherwise a wave
-    // owns both states of tiles wl, wl + 4, ...
-    static constexpr bool KV_SPLIT = NMT == 2;
+    // owns both states of tiles wl, wl + 4, ...  (At d = 128 one unit fills the compute unit and the
+    // split costs more than it saves: 256 sequences of 512 tokens, 63 slots 51.4 us with it, 48.5
+    // without, 512 of them 101 and 95.)
+    static constexpr bool KV_SPLIT = NMT == 2 && D <= 64;
     // Slot rows held in LDS (bla_device.h, slot folding), their tiles and reduction blocks
     static constexpr bool FOLD = slots_folded(SP);
     static constexpr int HP = slot_rows(SP), NHT = HP / 16, KBH = HP / 32;
