@@ -61,9 +61,11 @@ template <int D, int MP, int SP> struct Pair {
     // split costs more than it saves: 256 sequences of 512 tokens, 63 slots 51.4 us with it, 48.5
     // without, 512 of them 101 and 95.)
     static constexpr bool KV_SPLIT = NMT == 2 && D <= 64;
-    // Slot rows held in LDS (bla_device.h, slot folding), their tiles and reduction blocks
-    static constexpr bool FOLD = slots_folded(SP);
-    static constexpr int HP = slot_rows(SP), NHT = HP / 16, KBH = HP / 32;
+    // Slot rows held in LDS (bla_device.h, slot folding), their tiles and reduction blocks.  Not folded:
+    // 64 padded slots at d = 128, M = 64, where the LDS holds one unit either way (us folded / not: 780
+    // sequences of 81 tokens 103 / 98, 128 of 1024 87 / 86; M = 32 folded: 256 of 512 48.5 / 50.4).
+    static constexpr bool FOLD = slots_folded(SP) && !(D == 128 && MP == 64 && SP == 64);
+    static constexpr int HP = FOLD ? slot_rows(SP) : SP, NHT = HP / 16, KBH = HP / 32;
     static constexpr int ABROWS = FOLD ? HP + 1 : SP;  // with the last row
     // Row strides (elements): every row is 16 elements longer than its data, i.e. the stride
     // is 8 (mod 32) dwords.  With that stride a 16-lane group's 16-byte row-fragment reads
