@@ -66,7 +66,8 @@ CASES = [  # dtype, d, M, S, anchor
     (torch.bfloat16, 64, 32, 33, 0), (torch.bfloat16, 64, 32, 62, 1), (torch.bfloat16, 64, 20, 63, 0),
     (torch.bfloat16, 32, 64, 64, 1), (torch.bfloat16, 64, 64, 64, 0), (torch.bfloat16, 64, 64, 65, 1),
     (torch.bfloat16, 64, 64, 127, 0), (torch.bfloat16, 64, 64, 127, 1), (torch.bfloat16, 64, 64, 128, 0),
-    (torch.bfloat16, 128, 64, 127, 0), (torch.bfloat16, 64, 100, 64, 0), (torch.bfloat16, 64, 100, 128, 1),
+    (torch.bfloat16, 128, 64, 127, 0), (torch.bfloat16, 128, 64, 50, 1), (torch.bfloat16, 128, 64, 64, 0),
+    (torch.bfloat16, 128, 32, 63, 1), (torch.bfloat16, 64, 100, 64, 0), (torch.bfloat16, 64, 100, 128, 1),
     (torch.bfloat16, 128, 128, 64, 0), (torch.bfloat16, 128, 128, 63, 1), (torch.bfloat16, 128, 128, 127, 0),
     (torch.bfloat16, 128, 128, 128, 1), (torch.bfloat16, 128, 128, 255, 0), (torch.bfloat16, 128, 128, 256, 0),
     (torch.float32, 64, 32, 63, 0), (torch.float32, 64, 32, 64, 1), (torch.float32, 32, 64, 127, 1),
