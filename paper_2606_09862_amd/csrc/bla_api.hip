@@ -131,6 +131,40 @@ bla_status check_periods(const bla_params* p, const double* T)
     return BLA_OK;
 }
 
+// Blocks per segment of the summaries: enough summary workgroups to fill the device, within the scratch
+// cap; always a divisor of cps.  The pair kernel combines the summaries itself: one block per segment.
+// bf16 64-token summaries run D/32 column-slice workgroups per block.  Segments for two workgroups to a
+// compute unit (two) fill the device once by themselves, and past 32 blocks more of them only lengthen
+// the scan (4 sequences of 30000 tokens in 32-token chunks, d = 64, M = 32, 63 slots: 234 blocks 106 us,
+// 117 87).
+int summary_blocks(const Plan& pl, long long units, int nseg, int cps, long long cus, bool two)
+{
+    int bps = 1;
+    const size_t unit_bytes = pl.unit_floats * sizeof(float);
+    const long long slices = pl.bf16 && pl.C == kChunk ? pl.D / 32 : 1;
+    while (!pl.pair && units * (nseg - 1) * bps * slices < 2 * cus && cps % (2 * bps) == 0 &&
+           (size_t)units * (nseg - 1) * (2 * bps) * unit_bytes <= kMaxSummaryBytes && !(two && (nseg - 1) * 2 * bps > 32))
+        bps *= 2;
+    return bps;
+}
+
+// Whether sequences are cut for two one-unit workgroups to a compute unit, into w2 segments, rather than
+// for one, into w1.  That pays where it about halves a workgroup's chunks and the scan stays short, or about
+// as long as over the blocks of the w1 segments (us of a call, w1 / w2: 4 sequences of 8000 tokens in
+// 16-token chunks, d = M = 64, 127 slots 107 / 77, of 2000 (two chunks / one) 55 / 58; 12 of 3500 88 / 72; 6 of
+// 3500 in 32-token ones, M = 32, 63 slots (three / two) 38 / 45, 32 of 500 39 / 36; one of 14000 in 16-token ones 191 / 119 in float32; 2 of 30000 in 16-token ones,
+// d = 32, M = 16, 31 slots 75 / 80).
+bool two_per_cu(const Plan& pl, long long units, long long w1, long long w2, long long cus)
+{
+    const int c1 = (int)((pl.nch + w1 - 1) / w1), c2 = (int)((pl.nch + w2 - 1) / w2);
+    const int n1 = (pl.nch + c1 - 1) / c1, n2 = (pl.nch + c2 - 1) / c2;
+    if (c2 >= c1) return false;
+    if (n2 > 16 && c2 == 1) return false;
+    if (n2 <= 32) return c2 >= 3 || 3 * c1 >= 5 * c2;
+    if (n2 <= 64) return 3 * c1 >= 5 * c2;
+    return 5 * c1 >= 9 * c2 && (n2 <= 128 || 4 * n2 <= 5 * (n1 - 1) * summary_blocks(pl, units, n1, c1, cus, false));
+}
+
 // one_per_cu: aim at one sequence unit per compute unit instead of upw.
 void make_plan_for(const bla_params* p, bool step, bool one_per_cu, Plan* pl)
 {
@@ -171,11 +205,17 @@ void make_plan_for(const bla_params* p, bool step, bool one_per_cu, Plan* pl)
         const long long target = (long long)cus * (one_per_cu ? 1 : pl->pair ? pl->upw : wgs > 1 ? 2 : 1);
         if (units < target) {
             long long want = (target + units - 1) / units;
+            bool two = false;  // segments for two workgroups to a compute unit
             // Several one-unit workgroups to a compute unit: no more segments than run in one round (us at
             // d = 64, 1024 tokens; M = 32, 63 slots, 32-token chunks, uncut / two segments with two
             // workgroups to a compute unit: 300 sequences 143 / 157, 400 142 / 194; M = 16, 16-token chunks,
             // with three: 300 173 / 121, 400 171 / 237).
-            if (wgs > 1) want = units <= cus ? target / units : 2 * units <= (long long)cus * wgs ? 2 : 1;
+            if (wgs > 1) {
+                want = units <= cus ? target / units : 2 * units <= (long long)cus * wgs ? 2 : 1;
+                const long long one = (cus + units - 1) / units;
+                two = units <= cus && two_per_cu(*pl, units, one, want, cus);
+                if (units <= cus && !two) want = one;
+            }
             // A scan over the segments takes about 0.125 us each and a chunk of a segment 6.8 us
             // (d = M = 64): with few sequences, no more segments than balance the two
             // (4 sequences of 8192 tokens: 128 -> 64 segments,
@@ -197,16 +237,7 @@ void make_plan_for(const bla_params* p, bool step, bool one_per_cu, Plan* pl)
                             : nseg > kMaxPairSegments                                              ? kEnterScan
                                                                                                    : kEnterCombine;
             if (nseg > 1) {
-                // Blocks per segment: enough summary workgroups to fill the device, within
-                // the scratch cap; always a divisor of cps.
-                // The pair kernel combines the summaries itself: one block per segment.
-                // bf16 64-token summaries run D/32 column-slice workgroups per block.
-                int bps = 1;
-                const size_t unit_bytes = pl->unit_floats * sizeof(float);
-                const long long slices = pl->bf16 && pl->C == kChunk ? pl->D / 32 : 1;
-                while (!pl->pair && units * (nseg - 1) * bps * slices < 2 * cus && cps % (2 * bps) == 0 &&
-                       (size_t)units * (nseg - 1) * (2 * bps) * unit_bytes <= kMaxSummaryBytes)
-                    bps *= 2;
+                const int bps = summary_blocks(*pl, units, nseg, cps, cus, two);
                 pl->cpb = cps / bps;
                 pl->nbs = (nseg - 1) * bps;
             }

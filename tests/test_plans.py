@@ -67,6 +67,21 @@ def test_segments_of_the_one_unit_kernels_run_in_one_round():
             assert c[2] * p["nseg"] <= 768, (c, p["nseg"])
 
 
+def test_segments_for_two_workgroups_keep_the_scan_short():
+    """Few sequences in short chunks: twice the segments only where that halves a workgroup's chunks, and
+    no scan gets much longer than with half of them."""
+    def nseg(units, L, d, M, S, bf16, chunk):
+        return plans([("f", 1, units, L, d, M, S, bf16, chunk, 0)])[0]["nseg"]
+
+    assert nseg(4, 8000, 64, 64, 127, 1, 16) == 125 and nseg(4, 2000, 64, 64, 127, 1, 16) == 63
+    assert nseg(6, 3500, 64, 32, 63, 1, 32) == 37 and nseg(12, 3500, 64, 64, 127, 1, 16) == 37
+    assert nseg(2, 30000, 32, 16, 31, 1, 16) == 125 and nseg(1, 14000, 32, 32, 63, 0, 16) == 438
+    for units in (1, 2, 3, 5, 7, 12, 31, 64):
+        for L in (300, 2000, 3500, 9000, 30000, 60000):
+            n = nseg(units, L, 64, 32, 63, 1, 32)
+            assert units * n <= 512 and (n <= 128 or units <= 3)
+
+
 def test_products_that_the_vendor_library_takes():
     """The own kernel does not split a reduction, so past 1024 it loses at any number of tokens, and widths of 256
     and 512 go back to the library once many tokens hide its start."""
