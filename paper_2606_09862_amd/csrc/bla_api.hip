@@ -150,16 +150,16 @@ int summary_blocks(const Plan& pl, long long units, int nseg, int cps, long long
 
 // Whether sequences are cut for two one-unit workgroups to a compute unit, into w2 segments, rather than
 // for one, into w1.  That pays where it about halves a workgroup's chunks and the scan stays short, or about
-// as long as over the blocks of the w1 segments (us of a call, w1 / w2: 4 sequences of 8000 tokens in
-// 16-token chunks, d = M = 64, 127 slots 107 / 77, of 2000 (two chunks / one) 55 / 58; 12 of 3500 88 / 72; 6 of
-// 3500 in 32-token ones, M = 32, 63 slots (three / two) 38 / 45, 32 of 500 39 / 36; one of 14000 in 16-token ones 191 / 119 in float32; 2 of 30000 in 16-token ones,
-// d = 32, M = 16, 31 slots 75 / 80).
+// as long as over the blocks of the w1 segments.  Us of a call, w1 / w2: in 16-token chunks, d = M = 64, 127
+// slots, 4 sequences of 8000 tokens 107 / 77, of 2000 (two chunks / one) 55 / 58, 12 of 3500 88 / 72; in 32-token
+// ones, M = 32, 63 slots, 6 of 3500 (three / two) 38 / 45, 32 of 500 39 / 36; in float32, 16-token ones, 16 of 500
+// (two / one) 48 / 44, d = 32, one of 14000 191 / 119; 2 of 30000, d = 32, M = 16, 31 slots 75 / 80.
 bool two_per_cu(const Plan& pl, long long units, long long w1, long long w2, long long cus)
 {
     const int c1 = (int)((pl.nch + w1 - 1) / w1), c2 = (int)((pl.nch + w2 - 1) / w2);
     const int n1 = (pl.nch + c1 - 1) / c1, n2 = (pl.nch + c2 - 1) / c2;
     if (c2 >= c1) return false;
-    if (n2 > 16 && c2 == 1) return false;
+    if (n2 > (pl.bf16 ? 16 : 32) && c2 == 1) return false;
     if (n2 <= 32) return c2 >= 3 || 3 * c1 >= 5 * c2;
     if (n2 <= 64) return 3 * c1 >= 5 * c2;
     return 5 * c1 >= 9 * c2 && (n2 <= 128 || 4 * n2 <= 5 * (n1 - 1) * summary_blocks(pl, units, n1, c1, cus, false));
